@@ -34,6 +34,9 @@
 // 81k. Deeper rings of shorter slabs measured slower: the extra barriers cost
 // more than the added copy slack gains.)
 //
+// fp32 operands go through the same ring and are split in registers into three
+// bf16 terms each (below: Split), six bf16 MFMAs standing for eight fp32 ones.
+//
 // Accumulator layout of v_mfma_f32_32x32x{16_bf16,2_f32} (block of 32 x 32):
 // lane l, register r holds row (r & 3) + 8 * (r >> 2) + 4 * (l >> 5), column l & 31.
 // Both operands feed chunk (2s + (l >> 5)) of the slab at step s, so each lane
@@ -139,16 +142,6 @@ struct Mma<BF16> {
   __device__ __forceinline__ static void run(f32x16_t& acc, const v4u& a, const v4u& b) {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                   __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
-  }
-};
-
-template <>
-struct Mma<F32> {
-  __device__ __forceinline__ static void run(f32x16_t& acc, const v4u& a, const v4u& b) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
   }
 };
 
@@ -339,13 +332,156 @@ __device__ __forceinline__ void mma_step_mix(f32x16_t (&acc)[kMI][kNI], const Fr
   }
 }
 
-// LDS writes of this thread are complete, then the workgroup barrier. Unlike
-// __syncthreads() this does not wait for outstanding global loads, which keeps
-// the next slab's prefetch in flight across the barrier.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+// ------------------------------------------------------------------------- //
+// fp32 operands on the bf16 matrix cores
+// ------------------------------------------------------------------------- //
+// An fp32 value is split into three bf16 terms, x = h + m + l with h = bf16(x),
+// m = bf16(x - h), l = bf16(x - h - m) (both differences are exact; 3 x 8
+// significand bits hold fp32's 24, so the sum is x itself unless l underflows),
+// and a product is taken as the six terms hh, hm, mh, mm, hl, lh: the three left
+// out are below 2^-26 of it, less than one fp32 rounding. Each term is exact in the
+// bf16 MFMA's fp32 accumulation, which also rounds once per 16 products where the
+// fp32 MFMA rounds once per 2. Six 32x32x16 bf16 MFMAs take 6 x 32 cycles for what
+// takes eight 32x32x2 fp32 MFMAs 8 x 64, so the loop is bound by the bf16 matrix
+// rate / 6 instead of the fp32 one (256 flop/clk/CU). Measured on the 2048 x 151,936
+// head at 1536 tokens: a forward tile (K = 2048) 309 us, 222 TFLOP/s over the chip at
+// 85 % MFMA busy and a clock that power holds at 1.53 GHz; forward and backward of
+// 2048 tokens 28.7 -> 17.8 ms, with half the error against float64 (1.4e-6 -> 7.5e-7
+// on the hidden gradient).
+// An operand that is not finite, or too large for bf16, makes h or m infinite and
+// hence m or l NaN: every product it enters is NaN, so a wave whose accumulators
+// hold a NaN multiplies its part of the tile again with fp32 MFMAs (redo_f32).
+struct Split {
+  v4u p[3];  // 8 bf16 each: high, middle, low terms
+};
+
+// One term (a word of plane `part`) of two neighbouring elements; x0 and x1 become
+// what is left of them.
+__device__ __forceinline__ uint32_t split_term(float& x0, float& x1, int part) {
+  uint32_t w = pack_bf16x2(x0, x1);
+  if (part < 2) {
+    x0 -= __uint_as_float(w << 16);
+    x1 -= __uint_as_float(w & 0xffff0000u);
+    // Kept here: the compiler would otherwise sink the split to the step that uses it.
+    asm volatile("" : "+v"(w), "+v"(x0), "+v"(x1));
+  } else {
+    asm volatile("" : "+v"(w));
+  }
+  return w;
+}
+
+// The raw elements of one fragment of K16 step u (of two per slab): K8 steps 2u, 2u + 1.
+struct Raw {
+  v4u c[2];
+};
+template <bool Mn>
+__device__ __forceinline__ Raw read_raw(const v4u* l, int u, int wave_row0, int i, int lane) {
+  Raw r;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    if constexpr (Mn)
+      r.c[q] = read_frag_mn<F32>(l, 2 * u + q, wave_row0, i, lane);
+    else
+      r.c[q] = read_frag_k(l, 2 * u + q, wave_row0, i, lane);
+  }
+  return r;
+}
+// Term `part` of elements 2j, 2j + 1 of the fragment into word j of its plane
+// (j = 0 .. 3); x0 and x1 carry what is left from one term to the next.
+__device__ __forceinline__ void split_word(const Raw& r, Split& s, int j, int part, float& x0, float& x1) {
+  if (part == 0) {
+    x0 = __uint_as_float(r.c[j >> 1][2 * (j & 1)]);
+    x1 = __uint_as_float(r.c[j >> 1][2 * (j & 1) + 1]);
+  }
+  s.p[part][j] = split_term(x0, x1, part);
+}
+__device__ __forceinline__ void split_frag(const Raw& r, Split& s) {
+  float x0, x1;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int part = 0; part < 3; ++part) split_word(r, s, j, part, x0, x1);
+}
+
+constexpr int kSplitTerms = 6;
+constexpr int kTermA[kSplitTerms] = {2, 0, 1, 0, 1, 0};  // plane of A, smallest products first
+constexpr int kTermB[kSplitTerms] = {0, 2, 1, 1, 0, 0};  // plane of B
+constexpr int kSplitRow = kSplitTerms * kNI;             // MFMAs of one row of blocks
+
+// One K16 step: row of blocks by row of blocks, six terms of kNI MFMAs each. While
+// row r multiplies, the wave reads and splits B fragment r of the next step (into
+// bn) and A fragment r - 1 of the next step, whose row has been multiplied already;
+// row 0 splits this step's last A fragment, which the step before read (raw_a).
+// Reads go half a row (384 cycles of MFMAs) ahead of their splits, and each MFMA is
+// followed by one term of one word: a wave issues in order, so the five VALU
+// operations of a term fit into an MFMA's 32 cycles, and the eleven of a whole word
+// do not (issued word by word, the loop took 578k cycles per tile of K = 2048
+// against 393k of MFMAs).
+template <bool AMn, bool BMn, class Hook>
+__device__ __forceinline__ void split_step(f32x16_t (&acc)[kMI][kNI], Split (&a)[kMI], const Split (&bc)[kNI],
+                                           Split (&bn)[kNI], Raw& raw_a, const v4u* la, const v4u* lb, int u_next,
+                                           int wm, int wn, int lane, Hook&& hook) {
+  constexpr int kHalf = kSplitRow / 2;
+  static_assert(kMI == kNI && kHalf == 12, "one A and one B fragment per row, four words per half row");
+#pragma unroll
+  for (int r = 0; r < kMI; ++r) {
+    Raw raw_b;
+    float x0, x1;
+#pragma unroll
+    for (int q = 0; q < kSplitRow; ++q) {
+      const int term = q / kNI;
+      const int ni = term % 2 == 0 ? q % kNI : kNI - 1 - q % kNI;
+      acc[r][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a[r].p[kTermA[term]]),
+                                                           __builtin_bit_cast(bf16x8_t, bc[ni].p[kTermB[term]]),
+                                                           acc[r][ni], 0, 0, 0);
+      pin_order();
+      if (q == 0) raw_b = read_raw<BMn>(lb, u_next, wn * (kBN / kWavesN), r, lane);
+      if (q == kHalf) raw_a = read_raw<AMn>(la, u_next, wm * (kBM / 2), r, lane);
+      if (q < kHalf)
+        split_word(raw_a, a[(r + kMI - 1) % kMI], q / 3, q % 3, x0, x1);
+      else
+        split_word(raw_b, bn[r], (q - kHalf) / 3, q % 3, x0, x1);
+      hook(r * kSplitRow + q);
+      pin_order();
+    }
+  }
+}
+
+// The wave's part of the tile by fp32 MFMAs straight from global memory, for
+// operands that the split cannot hold. Lane half h takes k index k + h; rows past
+// the valid range read the last valid one.
+template <bool AMn, bool BMn>
+__device__ __forceinline__ void redo_f32(f32x16_t (&acc)[kMI][kNI], const float* a, int64_t lda, int64_t m_left,
+                                         const float* b, int64_t ldb, int64_t n_left, int64_t k_valid, int wm, int wn,
+                                         int lane) {
+  int64_t ra[kMI], rb[kNI];
+#pragma unroll
+  for (int i = 0; i < kMI; ++i) {
+    const int64_t r = wm * (kBM / 2) + 32 * i + (lane & 31);
+    ra[i] = (r < m_left ? r : m_left - 1) * (AMn ? 1 : lda);
+  }
+#pragma unroll
+  for (int i = 0; i < kNI; ++i) {
+    const int64_t r = wn * (kBN / kWavesN) + 32 * i + (lane & 31);
+    rb[i] = (r < n_left ? r : n_left - 1) * (BMn ? 1 : ldb);
+  }
+#pragma unroll
+  for (int i = 0; i < kMI; ++i)
+#pragma unroll
+    for (int j = 0; j < kNI; ++j) acc[i][j] = f32x16_t{};
+#pragma unroll 1
+  for (int64_t k = lane >> 5; k - (lane >> 5) < k_valid; k += 2) {
+    const bool in = k < k_valid;
+    float fa[kMI], fb[kNI];
+#pragma unroll
+    for (int i = 0; i < kMI; ++i) fa[i] = in ? a[ra[i] + k * (AMn ? lda : 1)] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) fb[i] = in ? b[rb[i] + k * (BMn ? ldb : 1)] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < kMI; ++i)
+#pragma unroll
+      for (int j = 0; j < kNI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
+  }
 }
 
 // One accumulator element, read out of its AGPR at this point of the program.
@@ -356,6 +492,15 @@ __device__ __forceinline__ float acc_read(float x) {
   float r;
   asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(r) : "a"(x));
   return r;
+}
+
+// LDS writes of this thread are complete, then the workgroup barrier. Unlike
+// __syncthreads() this does not wait for outstanding global loads, which keeps
+// the next slab's prefetch in flight across the barrier.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // Row index inside the 256-row tile of accumulator (mi, register r) for this lane.
@@ -553,11 +698,68 @@ __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*ld
     wait_slabs_barrier<kCopiesPerSlab>(pending);
   }
   epi_mark(epi, 0);
-  Frags f0, f1;
-  read_frags<E, AMn, BMn>(f0, lds[0], lds[0] + kAChunks, 0, wm, wn, lane);
   constexpr int kCopyNext = kCopiesPerSlab - kCopyNow;
   static_assert(kCopyNow > 0 && kCopyNext > 0 && (kMI * kNI) % kCopyNow == 0 && (kMI * kNI) % kCopyNext == 0,
                 "copies spread evenly over a step's MFMAs");
+  if constexpr (std::is_same<E, F32>::value) {
+    // The same ring and copy schedule with two K16 steps per slab, each of
+    // kMI * kSplitRow MFMAs: kCopyNow copies in the slab's last step, right after
+    // the barrier that frees the stage, the rest in the next slab's first step.
+    constexpr int kSplitMfmas = kMI * kSplitRow;
+    static_assert(kRowChunks == 8 && kSplitMfmas % kCopyNow == 0 && kSplitMfmas % kCopyNext == 0, "two steps per slab");
+    Split a[kMI], b0[kNI], b1[kNI];
+    Raw raw_a;
+#pragma unroll
+    for (int i = 0; i < kNI; ++i)
+      split_frag(read_raw<BMn>(lds[0] + kAChunks, 0, wn * (kBN / kWavesN), i, lane), b0[i]);
+#pragma unroll
+    for (int i = 0; i + 1 < kMI; ++i) split_frag(read_raw<AMn>(lds[0], 0, wm * (kBM / 2), i, lane), a[i]);
+    raw_a = read_raw<AMn>(lds[0], 0, wm * (kBM / 2), kMI - 1, lane);
+    uint32_t carry = 0;  // whether slab kt + 1 has copies left for this slab's first step
+    auto slab = [&](int kt, auto steady) {
+      constexpr bool kSteady = decltype(steady)::value;  // 1 <= kt <= nk - 4: every copy is issued
+      const int stage = kt % kStages;
+      const int cstage = (kt + 1) % kStages;
+      const char* ga1 = slab_ptr(true, kt + 1);
+      const char* gb1 = slab_ptr(false, kt + 1);
+      constexpr int kEveryNext = kSplitMfmas / kCopyNext;
+      split_step<AMn, BMn>(acc, a, b0, b1, raw_a, lds[stage], lds[stage] + kAChunks, 1, wm, wn, lane, [&](int t) {
+        if (t % kEveryNext == kEveryNext - 1 && (kSteady || carry))
+          copy_at(kCopyNow + t / kEveryNext, ga1, gb1, cstage);
+      });
+      const int kn = kt + kStages;
+      if (kSteady || kt + 1 < nk) {
+        const int rest = nk - kt - 2;
+        wait_slabs_barrier<kCopiesPerSlab>(rest < kStages - 2 ? rest : kStages - 2);
+      }
+      const uint32_t refill = kSteady ? 1u : uniform_u32(kn < nk - 1 || (kn == nk - 1 && !tail) ? 1u : 0u);
+      const char* ga2 = slab_ptr(true, kn);
+      const char* gb2 = slab_ptr(false, kn);
+      constexpr int kEveryNow = kSplitMfmas / kCopyNow;
+      split_step<AMn, BMn>(acc, a, b1, b0, raw_a, lds[cstage], lds[cstage] + kAChunks, 0, wm, wn, lane, [&](int t) {
+        if (t % kEveryNow == kEveryNow - 1 && (kSteady || refill)) copy_at(t / kEveryNow, ga2, gb2, stage);
+      });
+      if (!kSteady && kn == nk - 1 && tail) copy_slab(kn, stage);
+      carry = refill;
+    };
+    int kt = 0;
+    if (nk > 0) slab(kt++, std::false_type{});
+    for (; kt <= nk - 4; ++kt) slab(kt, std::true_type{});
+    for (; kt < nk; ++kt) slab(kt, std::false_type{});
+    // 0 for finite sums, NaN if any is NaN (or infinite).
+    float bad = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kMI; ++i)
+#pragma unroll
+      for (int j = 0; j < kNI; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bad = fmaf(0.0f, acc_read(acc[i][j][r]), bad);
+    if (__ballot(bad != 0.0f || bad != bad) != 0)
+      redo_f32<AMn, BMn>(acc, reinterpret_cast<const float*>(a_base), s.lda, m_valid - m0,
+                         reinterpret_cast<const float*>(b_base), s.ldb, n_valid - n0, k_valid, wm, wn, lane);
+  } else {
+  Frags f0, f1;
+  read_frags<E, AMn, BMn>(f0, lds[0], lds[0] + kAChunks, 0, wm, wn, lane);
   // Whether the previous iteration left copies of slab kt + 1 to step 0 (a
   // wave-uniform scalar, so that the copies' guards are scalar branches).
   uint32_t carry = 0;
@@ -611,6 +813,7 @@ __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*ld
   if (nk > 0) slab(kt++, std::false_type{});
   for (; kt <= nk - 4; ++kt) slab(kt, std::true_type{});
   for (; kt < nk; ++kt) slab(kt, std::false_type{});
+  }
   // Every copy has landed (the last wait drained them); once every wave's LDS
   // reads have returned, the epilogue may use LDS as scratch.
   lds_barrier();
