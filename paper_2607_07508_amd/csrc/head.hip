@@ -695,17 +695,41 @@ struct EpiAcc {
       }
       return;
     }
+    // A tile past the valid rows or columns: 32 x 32 block by block (blocks without
+    // a valid element are skipped), the 16 loads of a block from addresses clamped
+    // into it, so that they need no branches and stay in flight together, and the
+    // stores predicated. One load, add and store after another, each waiting for
+    // its load, took 70 us for the tiles of a 1000 x 64 output.
+    using gchar = __attribute__((address_space(1))) char;
+    using gfloat = __attribute__((address_space(1))) float;
 #pragma unroll
     for (int ni = 0; ni < kNI; ++ni) {
-      const int64_t n = n0 + acc_col(wn, ni, lane);
-      if (n >= n_valid) continue;
+      const int64_t nb = n0 + wn * (kBN / kWavesN) + ni * 32;
+      const int n_left = static_cast<int>(n_valid - nb < 32 ? n_valid - nb : 32);
+      if (n_left <= 0) continue;  // uniform
+      const int nl = lane & 31;
+      const uint32_t col = 4u * static_cast<uint32_t>(nl < n_left ? nl : n_left - 1);
 #pragma unroll
-      for (int mi = 0; mi < kMI; ++mi)
+      for (int mi = 0; mi < kMI; ++mi) {
+        const int64_t mb = m0 + wm * (kBM / 2) + mi * 32;
+        const int m_left = static_cast<int>(m_valid - mb < 32 ? m_valid - mb : 32);
+        if (m_left <= 0) continue;  // uniform
+        gchar* b = (gchar*)uniform_ptr(out + mb * ldo + nb);
+        float v[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int64_t m = m0 + acc_row(wm, mi, r, lane);
-          if (m < m_valid) out[m * ldo + n] = acc_read(acc[mi][ni][r]) + (overwrite ? 0.0f : out[m * ldo + n]);
+          const int m = (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
+          const uint32_t off = static_cast<uint32_t>(m < m_left ? m : m_left - 1) * static_cast<uint32_t>(4 * ldo) + col;
+          v[r] = overwrite ? 0.0f : *(const gfloat*)(b + off);
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
+          const float x = v[r] + acc_read(acc[mi][ni][r]);
+          if (nl < n_left && m < m_left)
+            *(gfloat*)(b + (static_cast<uint32_t>(m) * static_cast<uint32_t>(4 * ldo) + col)) = x;
+        }
+      }
     }
   }
 
