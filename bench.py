@@ -779,16 +779,17 @@ def main():
     out["breakdown"] = breakdown(step, T, H, V, esz, t_act, t_grad, torch)
     if args.timeline:
         vc0 = min(backward_vocab_block(chunk, V, H, esz), V)
-        # dH cuts K into pieces when a chunk's token tiles are few (the rule of csrc/layout.hpp)
-        pieces = min(max(-(-1024 // (-(-chunk // 256) * -(-H // 256))), 1), 8)
-        k_dh = vc0 if pieces == 1 else -(-(-(-vc0 // pieces)) // 64) * 64
         kernels = [("forward", B.KERNEL_HEAD_FORWARD, H)]
         if cfg.backward:
-            kernels += [("dz", B.KERNEL_BACKWARD_DZ, H), ("dH", B.KERNEL_BACKWARD_DH, k_dh),
+            kernels += [("dz", B.KERNEL_BACKWARD_DZ, H), ("dH", B.KERNEL_BACKWARD_DH, vc0),
                         ("dW", B.KERNEL_BACKWARD_DW, t_grad if len(chunks) == 1 else None)]
         out["timelines"] = {}
         for name, kid, k in kernels:
             r, khz = kernel_timeline(step, torch, dev, B, kid)
+            if name == "dH" and r.shape[0]:
+                # few token tiles: K is cut into pieces, each recording every tile once
+                pieces = max(1, r.shape[0] // len(set(r[:, 7].tolist())))
+                k = k if pieces == 1 else -(-(-(-k // pieces)) // 64) * 64
             out["timelines"][name] = timeline_summary(r, khz, k) if khz and r.shape[0] else None
     if args.vendor_gemm:
         log("vendor GEMM (context)")

@@ -101,8 +101,8 @@ struct GemmShape {
   int n_tiles;             // ceil(n / kBN) with the host bound
   int sn;                  // N tiles per XCD per raster wave (1, 2, 4 or 8)
   int msplit;              // 0: XCDs split the wave's N tiles; 1: XCDs split its M tiles
-  int64_t k_split;         // > 0: K is cut into pieces of this length (a multiple of 64),
-                           // piece blockIdx.y per workgroup; the epilogue keeps them apart
+  int64_t k_split;         // > 0: K is cut into pieces of this length (a multiple of 64);
+                           // the epilogue keeps them apart
 };
 
 // Tiles of one raster wave (256 blocks) along N and along M.
@@ -524,7 +524,7 @@ __device__ __forceinline__ void epi_mark(Epi& epi, int phase) {
 
 template <class E, bool AMn, bool BMn, class Epi>
 __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*lds)[kStageChunks], int mt,
-                                          int n_tile);
+                                          int n_tile, int piece = 0);
 
 // The generic kernel body: one 256 x 256 tile per workgroup. Epi provides:
 //   begin(n0, wm, wn, lane)                 before the K loop
@@ -551,11 +551,11 @@ __device__ __forceinline__ void gemm_body(const GemmShape& s, Epi& epi, v4u (*ld
   gemm_tile<E, AMn, BMn>(s, epi, lds, mt, n_tile);
 }
 
-// Tile (mt, n_tile) of the product, K piece blockIdx.y; nothing if the tile
-// lies past the valid rows.
+// Tile (mt, n_tile) of the product, K piece `piece` (with k_split); nothing if the
+// tile lies past the valid rows.
 template <class E, bool AMn, bool BMn, class Epi>
 __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*lds)[kStageChunks], int mt,
-                                          int n_tile) {
+                                          int n_tile, int piece) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = static_cast<int>(uniform_u32(static_cast<uint32_t>(tid >> 6)));  // keeps copy addresses scalar
@@ -567,7 +567,7 @@ __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*ld
   int64_t k_valid = s.k_dev ? static_cast<int64_t>(*s.k_dev) : s.k;
   int64_t k0 = 0;  // first K index of this workgroup's piece
   if (s.k_split > 0) {
-    k0 = static_cast<int64_t>(blockIdx.y) * s.k_split;
+    k0 = static_cast<int64_t>(piece) * s.k_split;
     k_valid = k_valid - k0 < s.k_split ? k_valid - k0 : s.k_split;
   }
   if (n_tile >= s.n_tiles || mt >= s.m_tiles) return;

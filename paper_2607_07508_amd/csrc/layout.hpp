@@ -52,22 +52,42 @@ inline LogprobLayout logprob_layout(int64_t T, int64_t H, int64_t V, size_t esiz
 // sao_loss_backward
 struct BackwardLayout {
   int64_t t_pad, n_count_blocks, vc, n_vblocks;
-  int dh_pieces;   // K pieces of the dH product (each with its own fp32 accumulator)
+  int64_t dh_cap;  // token tiles of dH accumulators (dh_cap_tiles)
   size_t blk_counts, count, next, idx, pos, g_c, lse_c, y_c, hg, dh, dz, total;
 };
 
-// K pieces of the dH product: enough that its output tiles number at least 1024
-// (four per CU) at the host bound of token rows, at most 8. Typically about a
-// third of a chunk's rows carry a gradient, so this leaves a short chunk's dH
-// launch with about one tile per CU.
-constexpr int kMaxDhPieces = 8;
-inline int dh_pieces(int64_t T, int64_t H) {
-  const int64_t tiles = ceil_div(T, kTile) * ceil_div(H, kTile);
-  int64_t p = ceil_div(1024, tiles);
-  if (p < 1) p = 1;
-  if (p > kMaxDhPieces) p = kMaxDhPieces;
-  return static_cast<int>(p);
+// K pieces of the dH product. Its output tiles (token tiles with a gradient row x
+// ceil(H / 256)) can be fewer than the CUs, so K (the block's vocabulary rows) is cut
+// into pieces, each adding into its own fp32 accumulator. Only the device knows how
+// many token tiles hold rows, so the kernels choose: of up to kMaxDhPieces pieces
+// whose accumulators fit `cap` token tiles, the number whose rounds of tiles over the
+// CUs take least, a round costing its K slabs and kDhRoundSlabs slabs' time of
+// prologue, epilogue and of the accumulators' later sum (25k cycles and 5k, a slab
+// taking about 2k). 24 tiles run as 10 pieces, 128 as 2, 136 as 7. The first
+// vocabulary block's K decides for all blocks.
+constexpr int kMaxDhPieces = 32;
+constexpr float kDhRoundSlabs = 16.0f;
+constexpr int dh_pieces(int m_tiles, int n_tiles, int64_t cap, int k_slabs) {
+  int best = 1;
+  float least = 0.0f;
+  for (int p = 1; p <= kMaxDhPieces && p <= k_slabs && (p == 1 || static_cast<int64_t>(p) * m_tiles <= cap); ++p) {
+    const int64_t rounds = (static_cast<int64_t>(m_tiles) * n_tiles * p + 255) / 256;
+    const float cost = static_cast<float>(rounds) * (static_cast<float>(k_slabs) / static_cast<float>(p) + kDhRoundSlabs);
+    if (p == 1 || cost < least) {
+      best = p;
+      least = cost;
+    }
+  }
+  return best;
 }
+// Token tiles of accumulators: every piece of up to 1024 output tiles (four per CU).
+constexpr int64_t dh_cap_tiles(int64_t m_tiles, int64_t n_tiles) {
+  int64_t c = (1024 + n_tiles - 1) / n_tiles;
+  if (c > m_tiles * kMaxDhPieces) c = m_tiles * kMaxDhPieces;
+  return c > m_tiles ? c : m_tiles;
+}
+// K rows per piece when `k` rows go into `pieces`: a multiple of 64.
+constexpr int64_t dh_piece_rows(int64_t k, int pieces) { return ((k + pieces - 1) / pieces + 63) / 64 * 64; }
 
 // MI355X's memory-side (Infinity) cache, shared by the XCDs, and its compute units.
 constexpr int64_t kMemorySideCacheBytes = int64_t{256} << 20;
@@ -111,7 +131,7 @@ inline BackwardLayout backward_layout(int64_t T, int64_t H, int64_t V, size_t es
   L.n_count_blocks = ceil_div(T, kRowsPerCountBlock);
   L.vc = vocab_block(L.t_pad, V, H, esize);
   L.n_vblocks = ceil_div(V, L.vc);
-  L.dh_pieces = dh_pieces(T, H);
+  L.dh_cap = dh_cap_tiles(L.t_pad / kTile, ceil_div(H, kTile));
   Carve c;
   const size_t tp = static_cast<size_t>(L.t_pad);
   L.blk_counts = c.take(4 * static_cast<size_t>(L.n_count_blocks));
@@ -123,7 +143,7 @@ inline BackwardLayout backward_layout(int64_t T, int64_t H, int64_t V, size_t es
   L.lse_c = c.take(4 * tp);
   L.y_c = c.take(4 * tp);
   L.hg = c.take(esize * tp * static_cast<size_t>(H));
-  L.dh = c.take(4 * tp * static_cast<size_t>(H) * static_cast<size_t>(L.dh_pieces));
+  L.dh = c.take(4 * static_cast<size_t>(kTile) * static_cast<size_t>(H) * static_cast<size_t>(L.dh_cap));
   L.dz = c.take(esize * tp * static_cast<size_t>(L.vc));
   L.total = c.off;
   return L;
