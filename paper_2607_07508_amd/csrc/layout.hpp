@@ -165,8 +165,16 @@ inline SegHead seg_head() {
   return H;
 }
 
-// sao_advantage needs only the head.
-inline size_t advantage_workspace() { return seg_head().total; }
+// The critic-free baselines need only the head.
+inline size_t baseline_workspace() { return seg_head().total; }
+
+// sao_advantage: the head, then (for more than one tile) a map per tile of tokens.
+constexpr int64_t kScanTileTokens = 2048;
+constexpr size_t kScanMapBytes = 64;
+inline size_t advantage_workspace(int64_t T) {
+  return seg_head().total +
+         (T > kScanTileTokens ? align256(kScanMapBytes * static_cast<size_t>(ceil_div(T, kScanTileTokens))) : 0);
+}
 
 // sao_clipped_loss
 struct LossLayout {

@@ -1,6 +1,6 @@
 // Skip-observation token-level GAE (Sec. 3.2, Eq. 4-5) as a segmented reverse scan.
 //
-// One workgroup per trajectory. Walking right to left, the state after a token is
+// Walking right to left, the state after a token is
 //   s = (Vn, R, A, G): value of the next action, reward pending since the next
 // action, and that action's advantage and return. Token t maps the state that
 // enters from its right to the state that leaves to its left:
@@ -108,6 +108,7 @@ constexpr int kScanThreads = 256;
 constexpr int kScanPer = 8;                               // tokens per thread per tile
 static_assert(kScanPer % 4 == 0, "whole blocks are read as 16-byte vectors");
 constexpr int kScanTile = kScanThreads * kScanPer;        // tokens per tile
+static_assert(kScanTile == kScanTileTokens, "the layout counts tiles");
 
 // State after applying map M to (Vn, R, A, G).
 struct St {
@@ -289,6 +290,361 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(4)
   }
 }
 
+// ------------------------------------------------------------------------- //
+// The flat scan: one workgroup per tile of kScanTile tokens, whatever trajectories
+// the tile holds
+// ------------------------------------------------------------------------- //
+// A trajectory's last token forgets the state entering from its right: a map that
+// covers such a token is marked `cut`, has no coefficients (z = X = Y = 0), and its
+// composition with anything on its right is itself, selected rather than multiplied,
+// so that NaN or infinite inputs stay inside their trajectory. A map that is not cut
+// lies in one trajectory, whose kappa the composition takes. Tile maps of a first
+// launch (k_scan_tiles) go to the workspace, 64 bytes each; in the second
+// (k_scan_flat) every tile composes the maps to its right, up to the end of its last
+// token's trajectory, and replays its tokens. A batch of one tile needs no first
+// launch, and the same workgroup checks the segments and counts the mask.
+//
+// Bound by launches and one tile's latency (load, compose, block scan, replay, about
+// 5 us) instead of by the longest trajectory's chain of tiles at 2.6 us each.
+struct CutMap {
+  Aff f;
+  int cut;
+};
+__device__ __forceinline__ CutMap cut_identity() { return CutMap{aff_identity(), 0}; }
+__device__ __forceinline__ CutMap compose_cut(const CutMap& F, const CutMap& G, double gamma, double kappa) {
+  const Aff c = compose(F.f, G.f, gamma, kappa);
+  CutMap r;
+  r.f.z = F.cut ? F.f.z : c.z;
+  r.f.cV = F.cut ? F.f.cV : c.cV;
+  r.f.cR = F.cut ? F.f.cR : c.cR;
+  r.f.X = F.cut ? F.f.X : c.X;
+  r.f.cA = F.cut ? F.f.cA : c.cA;
+  r.f.Y = F.cut ? F.f.Y : c.Y;
+  r.f.cG = F.cut ? F.f.cG : c.cG;
+  r.cut = F.cut | G.cut;
+  return r;
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ CutMap dpp_cut(const CutMap& x) {
+  return CutMap{dpp_aff<CTRL, ROW_MASK>(x.f), __builtin_amdgcn_update_dpp(0, x.cut, CTRL, ROW_MASK, 0xf, false)};
+}
+__device__ __forceinline__ CutMap wave_scan_cut(CutMap S, double gamma, double kappa) {
+  S = compose_cut(S, dpp_cut<0x111, 0xf>(S), gamma, kappa);
+  S = compose_cut(S, dpp_cut<0x112, 0xf>(S), gamma, kappa);
+  S = compose_cut(S, dpp_cut<0x114, 0xf>(S), gamma, kappa);
+  S = compose_cut(S, dpp_cut<0x118, 0xf>(S), gamma, kappa);
+  S = compose_cut(S, dpp_cut<0x142, 0xa>(S), gamma, kappa);
+  S = compose_cut(S, dpp_cut<0x143, 0xc>(S), gamma, kappa);
+  return S;
+}
+__device__ __forceinline__ St apply_cut(const CutMap& M, const St& s, double gamma, double kappa) {
+  return M.cut ? St{M.f.cV, M.f.cR, M.f.cA, M.f.cG} : apply(M.f, s, gamma, kappa);
+}
+
+struct TileMap {
+  Aff f;
+  int32_t cut;
+  int32_t count;  // loss-mask tokens
+};
+static_assert(sizeof(TileMap) == kScanMapBytes, "the layout counts these");
+
+// The trajectory holding token t, at or after trajectory lo (a batch whose segments
+// are malformed gives some trajectory in [lo, hi]).
+__device__ __forceinline__ int find_segment(const int32_t* cu, int lo, int hi, int64_t t) {
+  while (lo < hi) {  // the last b in [lo, hi] with cu[b] <= t
+    const int mid = lo + (hi - lo + 1) / 2;
+    if (static_cast<int64_t>(cu[mid]) <= t)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return lo;
+}
+
+__device__ __forceinline__ double segment_kappa(int64_t L, double gamma, double lam, double alpha) {
+  double lam_b = lam;
+  if (alpha > 0.0) {
+    lam_b = 1.0 - 1.0 / (alpha * static_cast<double>(L));
+    if (lam_b < 0.0) lam_b = 0.0;
+  }
+  return gamma * lam_b;
+}
+
+// One thread's kScanPer tokens [c0, c0 + kScanPer) and the trajectory of its last one.
+struct ScanTokens {
+  float v[kScanPer], r[kScanPer];
+  bool act[kScanPer];
+  int n;              // tokens below T
+  int seg;            // trajectory of token c0 + n - 1
+  int64_t s, e;       // its range
+  double kappa;
+
+  __device__ __forceinline__ void load(const float* values, const float* rewards, const uint8_t* mask, int64_t c0,
+                                       int64_t T, bool vec_ok) {
+    n = T - c0 >= kScanPer ? kScanPer : (T > c0 ? static_cast<int>(T - c0) : 0);
+    if (vec_ok && n == kScanPer) {
+      const f32x4_t* pv = reinterpret_cast<const f32x4_t*>(values + c0);
+      const f32x4_t* pr = reinterpret_cast<const f32x4_t*>(rewards + c0);
+      const uint64_t m8 = *reinterpret_cast<const uint64_t*>(mask + c0);
+#pragma unroll
+      for (int q = 0; q < kScanPer / 4; ++q) {
+        const f32x4_t vq = pv[q], rq = pr[q];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          v[4 * q + j] = vq[j];
+          r[4 * q + j] = rq[j];
+          act[4 * q + j] = ((m8 >> (8 * (4 * q + j))) & 0xffu) != 0;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < kScanPer; ++j) {
+        const bool in = j < n;
+        v[j] = in ? values[c0 + j] : 0.0f;
+        r[j] = in ? rewards[c0 + j] : 0.0f;
+        act[j] = in && mask[c0 + j] != 0;
+      }
+    }
+  }
+  __device__ __forceinline__ void locate(const int32_t* cu, int lo, int hi, int64_t c0, double gamma, double lam,
+                                         double alpha) {
+    seg = find_segment(cu, lo, hi, c0 + (n > 0 ? n - 1 : 0));
+    s = cu[seg];
+    e = cu[seg + 1];
+    kappa = segment_kappa(e - s, gamma, lam, alpha);
+  }
+  // Right to left over the tokens: end() before the last token of a trajectory, then
+  // act(j, kappa) or obs(j). The trajectory changes at most once per token.
+  template <class End, class Act, class Obs>
+  __device__ __forceinline__ void walk(const int32_t* cu, int64_t c0, double gamma, double lam, double alpha, End&& end,
+                                       Act&& action, Obs&& obs) const {
+    int b = seg;
+    int64_t bs = s, be = e;
+    double k = kappa;
+#pragma unroll
+    for (int j = kScanPer - 1; j >= 0; --j) {
+      if (j >= n) continue;
+      const int64_t t = c0 + j;
+      if (t < bs) {  // rarely: into the trajectory on the left
+        while (t < bs && b > 0) {  // (past empty ones)
+          --b;
+          be = bs;
+          bs = cu[b];
+        }
+        k = segment_kappa(be - bs, gamma, lam, alpha);
+      }
+      if (t + 1 == be) end();
+      if (act[j])
+        action(j, k);
+      else
+        obs(j);
+    }
+  }
+};
+
+// This thread's tokens as one map, and their loss-mask count.
+__device__ __forceinline__ CutMap thread_map(const ScanTokens& x, const int32_t* cu, int64_t c0, double gamma, double lam,
+                                             double alpha, int& cnt) {
+  CutMap F = cut_identity();
+  int c = 0;
+  x.walk(
+      cu, c0, gamma, lam, alpha, [&]() { F = CutMap{Aff{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, 1}; },
+      [&](int j, double k) {
+        ++c;
+        push_action(F.f, x.v[j], x.r[j], gamma, k);
+      },
+      [&](int j) { push_observation(F.f, x.r[j]); });
+  cnt = c;
+  return F;
+}
+
+// Trajectories of the first and last token of the tile at t0 (uniform).
+__device__ __forceinline__ void tile_segments(const int32_t* cu, int32_t B, int64_t T, int64_t t0, int& lo, int& hi) {
+  const int64_t last = t0 + kScanTile < T ? t0 + kScanTile - 1 : T - 1;
+  lo = find_segment(cu, 0, B - 1, t0);
+  hi = static_cast<int64_t>(cu[lo + 1]) > last ? lo : find_segment(cu, lo, B - 1, last);
+}
+
+// First launch: block i's tile map; the block after the last tile checks the segments.
+__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const float* values, const float* rewards,
+                                                             const uint8_t* mask, const int32_t* cu, int32_t B,
+                                                             int64_t T, double gamma, double lam, double alpha,
+                                                             TileMap* maps, int32_t* bad, int32_t* status, bool vec_ok) {
+  __shared__ CutMap s_agg[kScanThreads / 64];
+  __shared__ double s_kap[kScanThreads / 64];
+  __shared__ int s_cnt[kScanThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == gridDim.x - 1) {
+    const bool b = segments_bad<kScanThreads>(cu, B, T);
+    if (tid == 0) {
+      *bad = b ? 1 : 0;
+      if (b && status) atomicOr(status, SAO_STATUS_SEGMENTS);
+    }
+    return;
+  }
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kScanTile;
+  const int64_t c0 = t0 + static_cast<int64_t>(kScanThreads - 1 - tid) * kScanPer;
+  ScanTokens x;
+  x.load(values, rewards, mask, c0, T, vec_ok);
+  int lo, hi;
+  tile_segments(cu, B, T, t0, lo, hi);
+  x.locate(cu, lo, hi, c0, gamma, lam, alpha);
+  int cnt;
+  const CutMap S = wave_scan_cut(thread_map(x, cu, c0, gamma, lam, alpha, cnt), gamma, x.kappa);
+  cnt = wave_sum(cnt);
+  if (lane == 63) {
+    s_agg[wave] = S;
+    s_kap[wave] = x.kappa;
+  }
+  if (lane == 0) s_cnt[wave] = cnt;
+  __syncthreads();
+  if (tid == 0) {
+    CutMap m = s_agg[0];
+    int c = s_cnt[0];
+    for (int w = 1; w < kScanThreads / 64; ++w) {
+      m = compose_cut(s_agg[w], m, gamma, s_kap[w]);
+      c += s_cnt[w];
+    }
+    maps[blockIdx.x] = TileMap{m.f, m.cut, c};
+  }
+}
+
+// Second launch: outputs of one tile; block 0 adds the tiles' loss-mask counts. With
+// kSingle the batch is one tile and this is the only launch.
+template <bool kSingle>
+__global__ __launch_bounds__(kScanThreads) void k_scan_flat(const float* values, const float* rewards,
+                                                            const uint8_t* mask, const int32_t* cu, int32_t B,
+                                                            int64_t T, double gamma, double lam, double alpha,
+                                                            float* adv, float* ret, int64_t* n_tokens, TileMap* maps,
+                                                            const int32_t* bad, int32_t* status, bool vec_ok) {
+  constexpr int kWaves = kScanThreads / 64;
+  __shared__ CutMap s_agg[kWaves];
+  __shared__ double s_kap[kWaves];
+  __shared__ CutMap s_right[kWaves];
+  __shared__ int64_t s_cnt[kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kScanTile;
+  const int64_t c0 = t0 + static_cast<int64_t>(kWaves * 64 - 1 - tid) * kScanPer;
+  ScanTokens x;
+  x.load(values, rewards, mask, c0, T, vec_ok);
+  bool is_bad;
+  if constexpr (kSingle) {
+    is_bad = segments_bad<kScanThreads>(cu, B, T);
+    if (tid == 0 && is_bad && status) atomicOr(status, SAO_STATUS_SEGMENTS);
+  } else {
+    is_bad = *bad != 0;
+  }
+  if (!kSingle && blockIdx.x == 0 && n_tokens) {
+    int64_t c = 0;
+    for (int i = tid; i < static_cast<int>(gridDim.x); i += kScanThreads) c += maps[i].count;
+    c = wave_sum(c);
+    if (lane == 0) s_cnt[wave] = c;
+    __syncthreads();
+    if (tid == 0) {
+      int64_t tot = 0;
+      for (int w = 0; w < kWaves; ++w) tot += s_cnt[w];
+      *n_tokens = tot;
+    }
+  }
+  int lo = 0, hi = 0;
+  if (!is_bad) tile_segments(cu, B, T, t0, lo, hi);
+  int cnt = 0;
+  float oa[kScanPer], og[kScanPer];
+  if (is_bad) {
+#pragma unroll
+    for (int j = 0; j < kScanPer; ++j) {
+      cnt += x.act[j] ? 1 : 0;
+      oa[j] = og[j] = __builtin_nanf("");
+    }
+  } else {
+    x.locate(cu, lo, hi, c0, gamma, lam, alpha);
+    const CutMap S = wave_scan_cut(thread_map(x, cu, c0, gamma, lam, alpha, cnt), gamma, x.kappa);
+    const CutMap E = dpp_cut<0x138, 0xf>(S);  // the lanes to the right only (identity at lane 0)
+    if (lane == 63) {
+      s_agg[wave] = S;
+      s_kap[wave] = x.kappa;
+    }
+    // The state entering the tile from the right: the maps of the tiles to the right,
+    // 64 per wave and 256 per round, up to the one that ends this tile's last trajectory.
+    St right{0.0, 0.0, 0.0, 0.0};
+    if constexpr (!kSingle) {
+      const int64_t e_hi = cu[hi + 1];
+      const double k_hi = segment_kappa(e_hi - static_cast<int64_t>(cu[hi]), gamma, lam, alpha);
+      const int n_right = e_hi > t0 + kScanTile ? static_cast<int>((e_hi - 1) / kScanTile - blockIdx.x) : 0;
+      CutMap all = cut_identity();
+      for (int i0 = 0; i0 < n_right; i0 += kScanThreads) {  // uniform
+        // Scan order is right to left, so lane 63 takes the tile nearest to this one.
+        const int i = i0 + 64 * wave + 63 - lane;
+        CutMap M = cut_identity();
+        if (i < n_right) M = CutMap{maps[blockIdx.x + 1 + i].f, maps[blockIdx.x + 1 + i].cut};
+        M = wave_scan_cut(M, gamma, k_hi);
+        __syncthreads();  // the previous round's s_right has been read
+        if (lane == 63) s_right[wave] = M;
+        __syncthreads();
+        for (int w = 0; w < kWaves; ++w) all = compose_cut(all, s_right[w], gamma, k_hi);
+      }
+      right = apply_cut(all, St{0.0, 0.0, 0.0, 0.0}, gamma, k_hi);
+    }
+    __syncthreads();
+    // ... then the waves to the right (lower waves), then the lanes to the right.
+    St st = right;
+    for (int w = 0; w < wave; ++w) st = apply_cut(s_agg[w], st, gamma, s_kap[w]);
+    st = apply_cut(E, st, gamma, dpp_f64<0x138, 0xf>(x.kappa, x.kappa));
+#pragma unroll
+    for (int j = 0; j < kScanPer; ++j) oa[j] = og[j] = 0.0f;
+    x.walk(
+        cu, c0, gamma, lam, alpha, [&]() { st = St{0.0, 0.0, 0.0, 0.0}; },
+        [&](int j, double k) {
+          const double vv = x.v[j];
+          const double rt = static_cast<double>(x.r[j]) + st.R;
+          const double An = fma(k, st.A, fma(gamma, st.Vn, rt - vv));
+          const double Gn = fma(gamma, st.G, rt);
+          oa[j] = static_cast<float>(An);
+          og[j] = static_cast<float>(Gn);
+          st = St{vv, 0.0, An, Gn};
+        },
+        [&](int j) { st.R += static_cast<double>(x.r[j]); });
+  }
+  if (vec_ok && x.n == kScanPer) {
+    f32x4_t* qa = reinterpret_cast<f32x4_t*>(adv + c0);
+    f32x4_t* qg = reinterpret_cast<f32x4_t*>(ret + c0);
+#pragma unroll
+    for (int q = 0; q < kScanPer / 4; ++q) {
+      qa[q] = f32x4_t{oa[4 * q], oa[4 * q + 1], oa[4 * q + 2], oa[4 * q + 3]};
+      qg[q] = f32x4_t{og[4 * q], og[4 * q + 1], og[4 * q + 2], og[4 * q + 3]};
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kScanPer; ++j)
+      if (j < x.n) {
+        adv[c0 + j] = oa[j];
+        ret[c0 + j] = og[j];
+      }
+  }
+  if (kSingle && n_tokens) {
+    const int64_t wcnt = wave_sum(cnt);
+    __syncthreads();
+    if (lane == 0) s_cnt[wave] = wcnt;
+    __syncthreads();
+    if (tid == 0) {
+      int64_t tot = 0;
+      for (int w = 0; w < kWaves; ++w) tot += s_cnt[w];
+      *n_tokens = tot;
+    }
+  }
+}
+
+// The flat scan reads its inputs twice and keeps fewer waves per SIMD, so it moves
+// half as many tokens per second as one workgroup per trajectory when those fill the
+// GPU and are long (2^22 tokens: 48 us against 27 us with 512 trajectories or more;
+// 2^24: 134 us against 70 us with 1024, 134 us either way with 256). Up to 2^20
+// tokens both take a few launches' time whatever the lengths (23 us per call from
+// Python), but for one trajectory among few: 131,071 tokens in one took 183 us with
+// one workgroup and 19 us flat. So trajectories by the CU-full over 2^20 tokens take
+// one workgroup each, everything else the flat scan.
+constexpr int64_t kScanFlatTokens = int64_t{1} << 20;
+constexpr int32_t kScanFlatMaxB = 256;
+
 int launch_advantage(const float* values, const float* rewards, const uint8_t* mask,
                             const int32_t* cu_seqlens, int32_t B, int64_t T, double gamma, double lam,
                             double alpha, float* adv, float* ret, int64_t* n_tokens, int32_t* status,
@@ -297,12 +653,26 @@ int launch_advantage(const float* values, const float* rewards, const uint8_t* m
   char* w8 = static_cast<char*>(ws);
   int32_t* bad = reinterpret_cast<int32_t*>(w8 + H.bad);
   int64_t* slots = reinterpret_cast<int64_t*>(w8 + H.slots);
-  hipLaunchKernelGGL((k_check_segments<256, kCountSlots>), dim3(1), dim3(256), 0, st, cu_seqlens, B, T, bad, slots,
-                     status);
   // Vector access needs 16-byte aligned float arrays and an 8-byte aligned mask.
   const uintptr_t f = reinterpret_cast<uintptr_t>(values) | reinterpret_cast<uintptr_t>(rewards) |
                       reinterpret_cast<uintptr_t>(adv) | reinterpret_cast<uintptr_t>(ret);
   const bool vec_ok = (f & 15u) == 0 && (reinterpret_cast<uintptr_t>(mask) & 7u) == 0;
+  if (T <= kScanTile) {
+    hipLaunchKernelGGL(k_scan_flat<true>, dim3(1), dim3(kScanThreads), 0, st, values, rewards, mask, cu_seqlens, B, T,
+                       gamma, lam, alpha, adv, ret, n_tokens, nullptr, nullptr, status, vec_ok);
+    return hipGetLastError();
+  }
+  if (T <= kScanFlatTokens || B < kScanFlatMaxB) {
+    TileMap* maps = reinterpret_cast<TileMap*>(w8 + H.total);
+    const unsigned tiles = static_cast<unsigned>(ceil_div(T, kScanTile));
+    hipLaunchKernelGGL(k_scan_tiles, dim3(tiles + 1), dim3(kScanThreads), 0, st, values, rewards, mask, cu_seqlens, B, T,
+                       gamma, lam, alpha, maps, bad, status, vec_ok);
+    hipLaunchKernelGGL(k_scan_flat<false>, dim3(tiles), dim3(kScanThreads), 0, st, values, rewards, mask, cu_seqlens, B,
+                       T, gamma, lam, alpha, adv, ret, n_tokens, maps, bad, status, vec_ok);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((k_check_segments<256, kCountSlots>), dim3(1), dim3(256), 0, st, cu_seqlens, B, T, bad, slots,
+                     status);
   hipLaunchKernelGGL(k_advantage, dim3(B), dim3(kScanThreads), 0, st, values, rewards, mask, cu_seqlens,
                      B, T, gamma, lam, alpha, adv, ret, slots, bad, vec_ok);
   if (n_tokens) hipLaunchKernelGGL(k_slots_total<kCountSlots>, dim3(1), dim3(64), 0, st, slots, n_tokens);

@@ -7,21 +7,25 @@
 
 namespace sao {
 
+// Whether cu_seqlens does not rise from 0 to T without decreasing (uniform over the
+// block of THREADS threads).
+template <int THREADS>
+__device__ __forceinline__ bool segments_bad(const int32_t* cu, int32_t B, int64_t T) {
+  int b = threadIdx.x == 0 && (cu[0] != 0 || static_cast<int64_t>(cu[B]) != T) ? 1 : 0;
+  for (int32_t i = threadIdx.x; i < B; i += THREADS) b |= cu[i + 1] < cu[i] ? 1 : 0;
+  return __syncthreads_or(b) != 0;
+}
+
 // One block: cu_seqlens must rise from 0 to T without decreasing. Sets *bad (0/1),
 // zeroes the kSlots count slots, and flags the status word.
 template <int THREADS, int kSlots>
 __global__ __launch_bounds__(THREADS) void k_check_segments(const int32_t* cu, int32_t B, int64_t T, int32_t* bad,
                                                             int64_t* slots, int32_t* status) {
-  __shared__ int32_t s_bad;
-  if (threadIdx.x == 0) s_bad = (cu[0] != 0 || static_cast<int64_t>(cu[B]) != T) ? 1 : 0;
   for (int i = threadIdx.x; i < kSlots; i += THREADS) slots[i] = 0;
-  __syncthreads();
-  for (int32_t i = threadIdx.x; i < B; i += THREADS)
-    if (cu[i + 1] < cu[i]) atomicOr(&s_bad, 1);
-  __syncthreads();
+  const bool b = segments_bad<THREADS>(cu, B, T);
   if (threadIdx.x == 0) {
-    *bad = s_bad;
-    if (s_bad && status) atomicOr(status, SAO_STATUS_SEGMENTS);
+    *bad = b ? 1 : 0;
+    if (b && status) atomicOr(status, SAO_STATUS_SEGMENTS);
   }
 }
 

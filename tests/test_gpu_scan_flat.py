@@ -1,0 +1,79 @@
+"""The flat advantage scan (tiles of 2048 tokens whatever trajectories they hold)
+around its edges: one tile and a few more, trajectories that end at, before and
+after tile and thread boundaries, empty ones, a single one over hundreds of tiles,
+and the switch to one workgroup per trajectory; and non-finite inputs, which stay
+inside their trajectory."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2607_07508_amd as sao
+from tests.gpu_common import TOL_ADV, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(lengths, seed):
+    rng = np.random.default_rng(seed)
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    T = int(cu[-1])
+    mask = (rng.random(T) < 0.6).astype(np.uint8)
+    v = rng.normal(0.5, 0.2, T).astype(np.float32)
+    r = rng.normal(0.0, 0.1, T).astype(np.float32)
+    return v, r, mask, cu
+
+
+def _run(v, r, mask, cu, gamma, lam, alpha):
+    out = sao.advantage(*[torch.from_numpy(x).cuda() for x in (v, r, mask, cu)], gamma, lam, alpha)
+    torch.cuda.synchronize()
+    return [x.cpu().numpy() for x in out]
+
+
+CASES = {
+    "one token": [1],
+    "one tile exactly": [2048],
+    "tile and one": [2049],
+    "ends on tile edges": [2048, 4096, 2048],
+    "ends beside tile edges": [2047, 2, 2047, 4097, 1, 2046],
+    "short in one tile": [3, 1, 0, 0, 8, 7, 9, 250, 0, 1],
+    "empty at both ends": [0, 0, 5000, 0, 0, 1, 3000, 0],
+    "many short": [int(x) for x in np.random.default_rng(3).integers(0, 40, 700)],
+    "hundreds of tiles": [13, 700_001, 5],
+    "per trajectory": [4097] * 1030,  # over the token and trajectory limits of the flat scan
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("gamma,lam,alpha", [(1.0, 1.0, 1.5), (0.97, 0.9, 0.0), (0.0, 0.5, 0.0)])
+def test_flat_scan(name, gamma, lam, alpha):
+    v, r, mask, cu = _batch(CASES[name], len(name))
+    if len(mask) > 1_000_000 and (gamma, alpha) != (1.0, 1.5):
+        pytest.skip("one setting is enough at this size")
+    say(f"flat scan: {name}, T={len(mask)} gamma={gamma}")
+    adv, ret, n = _run(v, r, mask, cu, gamma, lam, alpha)
+    ra, rr, N = oracle.advantage(v, r, mask, cu, gamma, lam, alpha)
+    assert int(n[0]) == N
+    assert (np.abs(adv - ra) <= TOL_ADV * np.maximum(1.0, np.abs(ra))).all()
+    assert (np.abs(ret - rr) <= TOL_ADV * np.maximum(1.0, np.abs(rr))).all()
+
+
+@pytest.mark.parametrize("lengths", [[500, 20, 600], [3000, 20, 5000, 2000]])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_nonfinite_stays_in_its_trajectory(lengths, bad):
+    v, r, mask, cu = _batch(lengths, 9)
+    hit = [2] if len(lengths) == 3 else [1, 3]
+    for b in hit:
+        v[cu[b] + 7] = bad
+        r[cu[b] + 9] = bad
+        mask[cu[b] + 7] = 1
+    say(f"flat scan, {bad} in trajectories {hit} of {lengths}")
+    adv, ret, _ = _run(v, r, mask, cu, 1.0, 1.0, 1.5)
+    for b in range(len(lengths)):
+        s, e = cu[b], cu[b + 1]
+        if b in hit:
+            assert not np.isfinite(adv[s + 7])
+            continue
+        ra, rr, _ = oracle.advantage(v[s:e], r[s:e], mask[s:e], np.array([0, e - s], np.int32), 1.0, 1.0, 1.5)
+        assert (np.abs(adv[s:e] - ra) <= TOL_ADV * np.maximum(1.0, np.abs(ra))).all()
+        assert (np.abs(ret[s:e] - rr) <= TOL_ADV * np.maximum(1.0, np.abs(rr))).all()
