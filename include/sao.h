@@ -344,6 +344,13 @@ sao_status_t sao_loss_backward(const void* hidden, int64_t ld_hidden, const void
                                const float* g, int64_t T, int64_t H, int64_t V, sao_dtype_t dtype,
                                void* dhidden, float* dw_head, void* ws, size_t ws_bytes,
                                hipStream_t stream);
+/* The same with dw_head written rather than added to, for a gradient that starts with
+ * this call: dw_head needs no zeros (T == 0 leaves it untouched). */
+sao_status_t sao_loss_backward_store(const void* hidden, int64_t ld_hidden, const void* w_head,
+                                     int64_t ld_w, const int32_t* target, const float* lse,
+                                     const float* g, int64_t T, int64_t H, int64_t V,
+                                     sao_dtype_t dtype, void* dhidden, float* dw_head, void* ws,
+                                     size_t ws_bytes, hipStream_t stream);
 
 /*
  * Critic head for the PPO-style update with a learned value model (Sec. 2): a

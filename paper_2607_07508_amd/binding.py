@@ -23,7 +23,7 @@ STATUS_TARGET_RANGE, STATUS_SEGMENTS, STATUS_NONFINITE, STATUS_KEY_RANGE = 1, 2,
 FLAG_MASKED, FLAG_USED, FLAG_LOW, FLAG_HIGH, FLAG_NONFINITE = 0, 1, 2, 3, 4
 
 EXPORTS = ("sao_status_string", "sao_last_error_message", "sao_version", "sao_workspace_size",
-           "sao_token_logprob", "sao_advantage", "sao_clipped_loss", "sao_loss_backward",
+           "sao_token_logprob", "sao_advantage", "sao_clipped_loss", "sao_loss_backward", "sao_loss_backward_store",
            "sao_value_forward", "sao_value_loss", "sao_ppo_loss", "sao_explained_variance", "sao_step_advantage",
            "sao_group_advantage", "sao_running_mean_advantage", "sao_clipped_loss_noalloc",
            "sao_debug_time_kernel", "sao_debug_clock_samples")
@@ -54,6 +54,8 @@ _SIGS = {
                                                 _p, _p, _p, _p]),
     "sao_loss_backward": (ctypes.c_int, [_p, _i64, _p, _i64, _p, _p, _p, _i64, _i64, _i64,
                                          ctypes.c_int, _p, _p, _p, ctypes.c_size_t, _p]),
+    "sao_loss_backward_store": (ctypes.c_int, [_p, _i64, _p, _i64, _p, _p, _p, _i64, _i64, _i64,
+                                               ctypes.c_int, _p, _p, _p, ctypes.c_size_t, _p]),
     "sao_value_forward": (ctypes.c_int, [_p, _i64, _p, _i64, _i64, ctypes.c_int, _p, _p, ctypes.c_size_t, _p]),
     "sao_value_loss": (ctypes.c_int, [_p, _i64, _p, _p, _p, _p, _i64, _i64, _p, ctypes.c_int, _p, _p, _p, _p,
                                       ctypes.c_size_t, _p]),
@@ -399,7 +401,7 @@ def explained_variance(values: torch.Tensor, ret: torch.Tensor, mask: torch.Tens
 def loss_backward(hidden: torch.Tensor, w_head: torch.Tensor, target: torch.Tensor, lse: torch.Tensor,
                   g: torch.Tensor, dw_head: Optional[torch.Tensor] = None,
                   dhidden: Optional[torch.Tensor] = None):
-    """(dhidden [T,H] in hidden's dtype, dw_head [V,H] f32 +=; zeroed if not given)."""
+    """(dhidden [T,H] in hidden's dtype, dw_head [V,H] f32 +=; starts from zero if not given)."""
     T, H = hidden.shape
     V = w_head.shape[0]
     dt = _dtype_code(hidden)
@@ -412,13 +414,14 @@ def loss_backward(hidden: torch.Tensor, w_head: torch.Tensor, target: torch.Tens
     _vec(g, "g", torch.float32, T, dev)
     if dhidden is None:
         dhidden = torch.empty((T, H), dtype=hidden.dtype, device=dev)
-    if dw_head is None:
-        dw_head = torch.zeros((V, H), dtype=torch.float32, device=dev)
+    store = dw_head is None  # written whole (by a call with T == 0, here)
+    if store:
+        dw_head = (torch.empty if T else torch.zeros)((V, H), dtype=torch.float32, device=dev)
     _vec(dhidden, "dhidden", hidden.dtype, T * H, dev)
     _vec(dw_head, "dw_head", torch.float32, V * H, dev)
     ws = _workspace(workspace_size(OP_BACKWARD, T, H, V, dt), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
-        _check(lib().sao_loss_backward(
+        _check((lib().sao_loss_backward_store if store else lib().sao_loss_backward)(
             _ptr(hidden), _rows(hidden, "hidden"), _ptr(w_head), _rows(w_head, "w_head"), _ptr(target),
             _ptr(lse), _ptr(g), T, H, V, dt, _ptr(dhidden), _ptr(dw_head), _ptr(ws),
             0 if ws is None else ws.numel(), _stream(dev)))

@@ -86,6 +86,22 @@ sao_status_t check_discounts(double gamma, double lam, double alpha) {
   return SAO_OK;
 }
 
+sao_status_t backward(const char* name, const void* hidden, int64_t ld_hidden, const void* w_head, int64_t ld_w,
+                      const int32_t* target, const float* lse, const float* g, int64_t T, int64_t H, int64_t V,
+                      sao_dtype_t dtype, void* dhidden, float* dw_head, bool dw_store, void* ws, size_t ws_bytes,
+                      hipStream_t stream) {
+  if (!hidden || !w_head || !target || !lse || !g || !dhidden || !dw_head)
+    return fail(SAO_ERR_NULL, "hidden, w_head, target, lse, g, dhidden and dw_head are required");
+  if (sao_status_t s = check_head(hidden, ld_hidden, w_head, ld_w, T, H, V, dtype)) return s;
+  if (!aligned16(dhidden) || !aligned16(dw_head))
+    return fail(SAO_ERR_SHAPE, "dhidden and dw_head must be 16-byte aligned");
+  if (T == 0) return ok();
+  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_BACKWARD, T, H, V, dtype))) return s;
+  return device(sao::launch_backward(hidden, ld_hidden, w_head, ld_w, target, lse, g, T, H, V, dtype == SAO_BF16,
+                                     dhidden, dw_head, dw_store, ws, stream),
+                name);
+}
+
 }  // namespace
 
 extern "C" {
@@ -287,16 +303,16 @@ sao_status_t sao_loss_backward(const void* hidden, int64_t ld_hidden, const void
                                const int32_t* target, const float* lse, const float* g, int64_t T, int64_t H,
                                int64_t V, sao_dtype_t dtype, void* dhidden, float* dw_head, void* ws,
                                size_t ws_bytes, hipStream_t stream) {
-  if (!hidden || !w_head || !target || !lse || !g || !dhidden || !dw_head)
-    return fail(SAO_ERR_NULL, "hidden, w_head, target, lse, g, dhidden and dw_head are required");
-  if (sao_status_t s = check_head(hidden, ld_hidden, w_head, ld_w, T, H, V, dtype)) return s;
-  if (!aligned16(dhidden) || !aligned16(dw_head))
-    return fail(SAO_ERR_SHAPE, "dhidden and dw_head must be 16-byte aligned");
-  if (T == 0) return ok();
-  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_BACKWARD, T, H, V, dtype))) return s;
-  return device(sao::launch_backward(hidden, ld_hidden, w_head, ld_w, target, lse, g, T, H, V,
-                                     dtype == SAO_BF16, dhidden, dw_head, ws, stream),
-                "sao_loss_backward launch");
+  return backward("sao_loss_backward launch", hidden, ld_hidden, w_head, ld_w, target, lse, g, T, H, V, dtype, dhidden,
+                  dw_head, false, ws, ws_bytes, stream);
+}
+
+sao_status_t sao_loss_backward_store(const void* hidden, int64_t ld_hidden, const void* w_head, int64_t ld_w,
+                                     const int32_t* target, const float* lse, const float* g, int64_t T, int64_t H,
+                                     int64_t V, sao_dtype_t dtype, void* dhidden, float* dw_head, void* ws,
+                                     size_t ws_bytes, hipStream_t stream) {
+  return backward("sao_loss_backward_store launch", hidden, ld_hidden, w_head, ld_w, target, lse, g, T, H, V, dtype,
+                  dhidden, dw_head, true, ws, ws_bytes, stream);
 }
 
 sao_status_t sao_value_forward(const void* hidden, int64_t ld_hidden, const void* w_v, int64_t T, int64_t H,

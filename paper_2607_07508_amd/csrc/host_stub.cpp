@@ -20,7 +20,7 @@ int launch_logprob(const void*, int64_t, const void*, int64_t, const int32_t*, c
   return kNoDevice;
 }
 int launch_backward(const void*, int64_t, const void*, int64_t, const int32_t*, const float*, const float*, int64_t,
-                    int64_t, int64_t, bool, void*, float*, void*, hipStream_t) {
+                    int64_t, int64_t, bool, void*, float*, bool, void*, hipStream_t) {
   return kNoDevice;
 }
 int launch_advantage(const float*, const float*, const uint8_t*, const int32_t*, int32_t, int64_t, double, double,

@@ -14,9 +14,10 @@ int launch_logprob(const void* hidden, int64_t ld_hidden, const void* w_head, in
                           const int32_t* target, const uint8_t* mask, int64_t T, int64_t H, int64_t V,
                           bool bf16, float* logp, float* lse, int32_t* status, void* ws, hipStream_t st);
 
+// dw_store: dw is written rather than added to.
 int launch_backward(const void* hidden, int64_t ld_hidden, const void* w_head, int64_t ld_w,
                            const int32_t* target, const float* lse, const float* g, int64_t T, int64_t H,
-                           int64_t V, bool bf16, void* dhidden, float* dw, void* ws, hipStream_t st);
+                           int64_t V, bool bf16, void* dhidden, float* dw, bool dw_store, void* ws, hipStream_t st);
 
 int launch_advantage(const float* values, const float* rewards, const uint8_t* mask,
                             const int32_t* cu_seqlens, int32_t B, int64_t T, double gamma, double lam,
