@@ -411,60 +411,72 @@ __device__ __forceinline__ float dot_chunk<F32>(const v4u& a, const v4u& b) {
   return s;
 }
 
-// 64 compacted rows per block, lane l of every wave on row l. Phase 1: wave w
-// merges the row's partials of vocabulary tiles w, w + 4, w + 8, ... in that
-// order (8 loads in flight; the 64 lanes read 256 contiguous bytes of a tile's
-// partials, [tile][row]), then the four waves' results are merged in wave order.
-// Phase 2: the target logits as dot products, 8 lanes per row and 8 rows per
-// wave at a time (each lane takes every 8th 16-byte chunk of the row), then
-// logp = z_y - lse at the row's position.
-constexpr int kFinRows = 64;
-template <class E>
+// kRows compacted rows per block, thread i on row i % kRows. Phase 1: the 256 / kRows
+// threads of a row merge its partials, thread q those of vocabulary tiles q, q + 256 /
+// kRows, ... in that order (8 loads in flight; neighbouring threads read contiguous
+// bytes of a tile's partials, [tile][row]), then the threads' results are merged in
+// a fixed tree. Phase 2: the target logits as dot products, kLanes lanes per row (each takes
+// every kLanes-th 16-byte chunk of the row), then logp = z_y - lse at the row's
+// position. Many rows: 64 per block, which reads a tile's partials in 512-byte runs
+// (94 us at 65,536 tokens, 106 us with 8). Few rows leave a serial chain of loads per
+// thread and most CUs idle, so up to kFinFewRows token rows a block takes 8 (2048
+// tokens 61 -> 12 us, 8192 58 -> 19, 16,384 56 -> 32).
+constexpr int64_t kFinFewRows = 32768;
+template <class E, int kRows>
 __global__ __launch_bounds__(256) void k_fwd_finalize(const float2* part, int64_t ldp, int m_groups,
                                                       const typename E::storage* hc, int64_t H,
                                                       const typename E::storage* w, int64_t ld_w,
                                                       int64_t V, const int32_t* idx,
                                                       const int32_t* target, const int32_t* count,
                                                       float* logp, float* lse, int32_t* status) {
-  constexpr int kWaves = 4;
+  constexpr int kPerRow = 256 / kRows;  // threads that merge a row
   constexpr int kInFlight = 8;
-  __shared__ float2 s_ms[kWaves][kFinRows];
-  __shared__ float s_lse[kFinRows];
+  constexpr int kLanes = kRows == 8 ? 32 : 8;  // lanes of a row's dot product
+  __shared__ float2 s_ms[4][kRows];  // per wave
+  __shared__ float s_lse[kRows];
   const int64_t n = *count;
-  const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kFinRows;
+  const int64_t c0 = static_cast<int64_t>(blockIdx.x) * kRows;
   if (c0 >= n) return;  // uniform over the block
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   {
-    const int64_t c = c0 + lane;
+    const int row = threadIdx.x % kRows, q = threadIdx.x / kRows;
+    const int64_t c = c0 + row;
     float m = -__builtin_inff(), s = 0.0f;
     if (c < n) {
-      int gi = wave;
-      for (; gi + (kInFlight - 1) * kWaves < m_groups; gi += kInFlight * kWaves) {
+      int gi = q;
+      for (; gi + (kInFlight - 1) * kPerRow < m_groups; gi += kInFlight * kPerRow) {
         float2 p[kInFlight];
 #pragma unroll
-        for (int u = 0; u < kInFlight; ++u) p[u] = part[static_cast<int64_t>(gi + u * kWaves) * ldp + c];
+        for (int u = 0; u < kInFlight; ++u) p[u] = part[static_cast<int64_t>(gi + u * kPerRow) * ldp + c];
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) lse_merge(m, s, p[u].x, p[u].y);
       }
-      for (; gi < m_groups; gi += kWaves) {
+#pragma unroll 4
+      for (; gi < m_groups; gi += kPerRow) {
         const float2 p = part[static_cast<int64_t>(gi) * ldp + c];
         lse_merge(m, s, p.x, p.y);
       }
     }
-    s_ms[wave][lane] = make_float2(m, s);
-  }
-  __syncthreads();
-  if (wave == 0) {
-    float m = s_ms[0][lane].x, s = s_ms[0][lane].y;
 #pragma unroll
-    for (int q = 1; q < kWaves; ++q) lse_merge(m, s, s_ms[q][lane].x, s_ms[q][lane].y);
-    s_lse[lane] = m + logf(s);
+    for (int d = kRows; d < 64; d <<= 1) {  // the row's threads of this wave
+      const float m2 = __shfl_xor(m, d, 64), s2 = __shfl_xor(s, d, 64);
+      lse_merge(m, s, m2, s2);
+    }
+    if (lane < kRows) s_ms[wave][lane] = make_float2(m, s);
   }
   __syncthreads();
-  const int sub = lane & 7;                 // lane within the row's group of 8
+  if (threadIdx.x < kRows) {
+    float m = s_ms[0][threadIdx.x].x, s = s_ms[0][threadIdx.x].y;
+#pragma unroll
+    for (int q = 1; q < 4; ++q) lse_merge(m, s, s_ms[q][threadIdx.x].x, s_ms[q][threadIdx.x].y);
+    s_lse[threadIdx.x] = m + logf(s);
+  }
+  __syncthreads();
+  constexpr int kWaveRows = 64 / kLanes;    // rows that a wave takes at a time
+  const int sub = lane & (kLanes - 1);
   const int64_t chunks = H / E::kPerChunk;  // 16-byte chunks per row
-  for (int j = 0; j < kFinRows / kWaves; j += 8) {
-    const int r = wave * (kFinRows / kWaves) + j + (lane >> 3);  // row of this block
+  for (int j = 0; j < kRows / 4; j += kWaveRows) {
+    const int r = wave * (kRows / 4) + j + lane / kLanes;  // row of this block
     const int64_t c = c0 + r;
     float z = 0.0f;
     int64_t t = 0;
@@ -476,12 +488,12 @@ __global__ __launch_bounds__(256) void k_fwd_finalize(const float2* part, int64_
       if (yok) {
         const v4u* hr = reinterpret_cast<const v4u*>(hc + c * H);
         const v4u* wr = reinterpret_cast<const v4u*>(w + static_cast<int64_t>(y) * ld_w);
-        for (int64_t k = sub; k < chunks; k += 8) z += dot_chunk<E>(hr[k], wr[k]);
+#pragma unroll 4
+        for (int64_t k = sub; k < chunks; k += kLanes) z += dot_chunk<E>(hr[k], wr[k]);
       }
     }
-    z += __shfl_xor(z, 4, 64);
-    z += __shfl_xor(z, 2, 64);
-    z += __shfl_xor(z, 1, 64);
+#pragma unroll
+    for (int d = kLanes / 2; d > 0; d >>= 1) z += __shfl_xor(z, d, 64);
     if (sub == 0 && c < n) {
       const float l = s_lse[r];
       const bool finite = __builtin_isfinite(l);
@@ -876,7 +888,12 @@ void k_bwd_dh(GemmShape s, EpiAcc<false> epi, DhPlan plan, int64_t* clk, int64_t
 }
 
 // dhidden[t] = sum over the K pieces (in order) of dH[pos[t]], rounded to the
-// element type, or zeros when pos[t] < 0.
+// element type, or zeros when pos[t] < 0. A wave takes a row's columns of one
+// kScatterCols span (blockIdx.y), every lane with the loads of kScatterCols / 256
+// quads of two pieces in flight: with one at a time a short pass, which has many
+// pieces, waited for each (one
+// 1531-token pass 31 -> 18 us).
+constexpr int kScatterCols = 1024;
 template <class E>
 __global__ __launch_bounds__(256) void k_dh_scatter(const float* dh, int64_t H, const int32_t* pos,
                                                     int64_t T, const int32_t* count, DhPlan plan,
@@ -885,18 +902,27 @@ __global__ __launch_bounds__(256) void k_dh_scatter(const float* dh, int64_t H, 
   const int64_t stride = static_cast<int64_t>(plan.m_tiles(*count)) * kBM * H;
   const int64_t t = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
+  constexpr int kQuads = kScatterCols / 256;
   const int32_t c = pos[t];
-  typename E::storage* out = dhid + t * H;
-  for (int64_t k = threadIdx.x & 63; k < H / 4; k += 64) {
-    float d[4] = {0.f, 0.f, 0.f, 0.f};
-    if (c >= 0) {
-      for (int q = 0; q < pieces; ++q) {
-        const float4 v = reinterpret_cast<const float4*>(dh + q * stride + static_cast<int64_t>(c) * H)[k];
-        d[0] += v.x; d[1] += v.y; d[2] += v.z; d[3] += v.w;
+  const int64_t k0 = static_cast<int64_t>(blockIdx.y) * (kScatterCols / 4) + (threadIdx.x & 63);
+  const int64_t last = H / 4 - 1;
+  float d[kQuads][4] = {};
+  if (c >= 0) {
+    const float4* src = reinterpret_cast<const float4*>(dh + static_cast<int64_t>(c) * H);
+#pragma unroll 2
+    for (int q = 0; q < pieces; ++q) {
+      const float4* p = src + q * (stride / 4);
+#pragma unroll
+      for (int u = 0; u < kQuads; ++u) {
+        const int64_t k = k0 + 64 * u;
+        const float4 v = p[k < last ? k : last];  // past the row: read, not stored
+        d[u][0] += v.x; d[u][1] += v.y; d[u][2] += v.z; d[u][3] += v.w;
       }
     }
-    store4<E>(out + 4 * k, d);
   }
+#pragma unroll
+  for (int u = 0; u < kQuads; ++u)
+    if (k0 + 64 * u <= last) store4<E>(dhid + t * H + 4 * (k0 + 64 * u), d[u]);
 }
 
 // ------------------------------------------------------------------------- //
@@ -1007,8 +1033,9 @@ static hipError_t logprob_impl(const void* hidden, int64_t ld_hidden, const void
                        full_tiles, static_cast<int64_t*>(nullptr), int64_t{0});
   }
   if (timed) (void)hipEventRecord(tm.stop, st);
-  hipLaunchKernelGGL(k_fwd_finalize<E>, dim3(static_cast<unsigned>(L.t_pad / kFinRows)), dim3(256), 0, st, part,
-                     L.t_pad,
+  const auto finalize = T <= kFinFewRows ? k_fwd_finalize<E, 8> : k_fwd_finalize<E, 64>;
+  const int64_t fin_rows = T <= kFinFewRows ? 8 : 64;
+  hipLaunchKernelGGL(finalize, dim3(static_cast<unsigned>(L.t_pad / fin_rows)), dim3(256), 0, st, part, L.t_pad,
                      static_cast<int>(L.m_tiles), hc, H, static_cast<const S*>(w_head), ld_w, V, idx,
                      target, count, logp, lse, status);
   return hipGetLastError();
@@ -1127,7 +1154,8 @@ static hipError_t backward_impl(const void* hidden, int64_t ld_hidden, const voi
     hook(vb, SAO_KERNEL_BACKWARD_DW, true);
   }
   const int t4 = static_cast<int>(ceil_div(T, 4));
-  hipLaunchKernelGGL(k_dh_scatter<E>, dim3(t4), dim3(256), 0, st, dh, H, pos, T, count, plan,
+  const unsigned spans = static_cast<unsigned>(ceil_div(H, kScatterCols));
+  hipLaunchKernelGGL(k_dh_scatter<E>, dim3(t4, spans), dim3(256), 0, st, dh, H, pos, T, count, plan,
                      static_cast<S*>(dhidden));
   return hipGetLastError();
 }
