@@ -526,6 +526,11 @@ template <class E, bool AMn, bool BMn, class Epi>
 __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*lds)[kStageChunks], int mt,
                                           int n_tile, int piece = 0);
 
+// The tiles of one gemm_tiles call. OneTile: no tile after the first.
+struct OneTile {
+  static constexpr bool kStream = false;
+};
+
 // The generic kernel body: one 256 x 256 tile per workgroup. Epi provides:
 //   begin(n0, wm, wn, lane)                 before the K loop
 //   tile(acc, m0, n0, wm, wn, lane, lds)    after it (LDS is free)
@@ -552,10 +557,19 @@ __device__ __forceinline__ void gemm_body(const GemmShape& s, Epi& epi, v4u (*ld
 }
 
 // Tile (mt, n_tile) of the product, K piece `piece` (with k_split); nothing if the
-// tile lies past the valid rows.
-template <class E, bool AMn, bool BMn, class Epi>
-__device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*lds)[kStageChunks], int mt,
-                                          int n_tile, int piece) {
+// tile lies past the valid rows. Or (Tiles::kStream) that tile and those that `tiles`
+// names after it, all of 256 valid rows on both sides (or rows that may be read): the
+// first slabs of the next tile are copied into the ring as soon as this tile's K loop
+// has left it, so that they are on their way during the epilogue. `tiles` provides
+//   claim()                 when a tile starts: ask for the next one
+//   next(mt, n_tile)        after its K loop (workgroup barriers allowed): whether there is one
+//   begin(), end()          around each tile
+//   scratch()               LDS for the epilogue, outside the ring
+// and the epilogue's settle() has what begin() loaded arrive.
+template <class E, bool AMn, bool BMn, class Epi, class Tiles>
+__device__ __forceinline__ void gemm_tiles(const GemmShape& s, Epi& epi, v4u (*lds)[kStageChunks], int mt,
+                                           int n_tile, int piece, Tiles&& tiles) {
+  constexpr bool kStream = std::remove_reference_t<Tiles>::kStream;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = static_cast<int>(uniform_u32(static_cast<uint32_t>(tid >> 6)));  // keeps copy addresses scalar
@@ -571,21 +585,13 @@ __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*ld
     k_valid = k_valid - k0 < s.k_split ? k_valid - k0 : s.k_split;
   }
   if (n_tile >= s.n_tiles || mt >= s.m_tiles) return;
-  const int64_t n0 = static_cast<int64_t>(n_tile) * kBN;
-  const int64_t m0 = static_cast<int64_t>(mt) * kBM;
+  int64_t n0 = static_cast<int64_t>(n_tile) * kBN;
+  int64_t m0 = static_cast<int64_t>(mt) * kBM;
   if (n0 >= n_valid || m0 >= m_valid || k_valid <= 0) return;
 
   constexpr int P = E::kPerChunk;
   const int64_t k_chunks = (k_valid + P - 1) / P;          // valid 16-byte chunks per row
   const int nk = static_cast<int>((k_chunks + kRowChunks - 1) / kRowChunks);  // slabs
-
-  epi.begin(n0, wm, wn, lane);
-
-  f32x16_t acc[kMI][kNI];
-#pragma unroll
-  for (int i = 0; i < kMI; ++i)
-#pragma unroll
-    for (int j = 0; j < kNI; ++j) acc[i][j] = f32x16_t{};
 
   const int esz = static_cast<int>(sizeof(typename E::storage));
   // The scalar bases point at the tile's first row (K-major) or column
@@ -621,7 +627,7 @@ __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*ld
     } else {
       const int r = (wave * Q + q) * kRowsPerCopy + lane / kRowChunks;
       lc = swz(r, lane % kRowChunks);
-      const int64_t row = row0 + r < valid ? r : valid - 1 - row0;  // from the tile's first row
+      const int64_t row = kStream || row0 + r < valid ? r : valid - 1 - row0;  // from the tile's first row
       off = static_cast<uint32_t>(row * ld * esz + static_cast<int64_t>(lc) * P * esz);
     }
   };
@@ -690,8 +696,20 @@ __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*ld
   // barrier inside iteration kt), its stage takes slab kt + kStages. Before that
   // barrier this wave's copies of slab kt+1 must have landed; the ones issued
   // after them (slabs kt+2 and kt+3, as far as they exist) may stay in flight.
-  for (int j = 0; j < kStages; ++j)
-    if (j < nk) copy_slab(j, j);
+  auto copy_first = [&]() {
+    for (int j = 0; j < kStages; ++j)
+      if (j < nk) copy_slab(j, j);
+  };
+  copy_first();
+  for (;;) {
+  if constexpr (kStream) tiles.begin();
+  epi.begin(n0, wm, wn, lane);
+  if constexpr (kStream) tiles.claim();
+  f32x16_t acc[kMI][kNI];
+#pragma unroll
+  for (int i = 0; i < kMI; ++i)
+#pragma unroll
+    for (int j = 0; j < kNI; ++j) acc[i][j] = f32x16_t{};
   {
     int pending = nk - 1 < kStages - 1 ? nk - 1 : kStages - 1;
     if (tail && nk <= kStages) pending = 0;  // the partial slab is among these copies
@@ -818,8 +836,34 @@ __device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*ld
   // reads have returned, the epilogue may use LDS as scratch.
   lds_barrier();
   epi_mark(epi, 1);
-  epi.tile(acc, m0, n0, wm, wn, lane, reinterpret_cast<void*>(&lds[0][0]));
-  epi.finish(mt, n0, wm, wn, lane, reinterpret_cast<void*>(&lds[0][0]));
+  if constexpr (!kStream) {
+    epi.tile(acc, m0, n0, wm, wn, lane, reinterpret_cast<void*>(&lds[0][0]));
+    epi.finish(mt, n0, wm, wn, lane, reinterpret_cast<void*>(&lds[0][0]));
+    break;
+  } else {
+    const int mt_done = mt;
+    const int64_t m_done = m0, n_done = n0;
+    epi.settle();
+    const bool more = tiles.next(mt, n_tile);  // uniform
+    if (more) {
+      m0 = static_cast<int64_t>(mt) * kBM;
+      n0 = static_cast<int64_t>(n_tile) * kBN;
+      a_base = static_cast<const char*>(s.a) + m0 * s.lda * esz;
+      b_base = static_cast<const char*>(s.b) + n0 * s.ldb * esz;
+      copy_first();
+    }
+    epi.tile(acc, m_done, n_done, wm, wn, lane, tiles.scratch());
+    epi.finish(mt_done, n_done, wm, wn, lane, tiles.scratch());
+    tiles.end();
+    if (!more) break;
+  }
+  }
+}
+
+template <class E, bool AMn, bool BMn, class Epi>
+__device__ __forceinline__ void gemm_tile(const GemmShape& s, Epi& epi, v4u (*lds)[kStageChunks], int mt,
+                                          int n_tile, int piece) {
+  gemm_tiles<E, AMn, BMn>(s, epi, lds, mt, n_tile, piece, OneTile{});
 }
 
 }  // namespace sao

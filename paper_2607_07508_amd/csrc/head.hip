@@ -178,6 +178,7 @@ struct EpiLse {
   float rm[kNI], rs[kNI];
 
   __device__ __forceinline__ void mark(int phase) { clock.mark(phase); }
+  __device__ __forceinline__ void settle() {}
 
   __device__ __forceinline__ void begin(int64_t, int, int, int) {
 #pragma unroll
@@ -241,11 +242,11 @@ struct EpiLse {
       lse_merge(rm[ni], rs[ni], m2, s2);
     }
     float2* sh = static_cast<float2*>(smem);
-    __syncthreads();
+    lds_barrier();  // not __syncthreads(): copies of the next tile may be in flight
     if (wm == 1 && lane < 32)
 #pragma unroll
       for (int ni = 0; ni < kNI; ++ni) sh[acc_col(wn, ni, lane)] = make_float2(rm[ni], rs[ni]);
-    __syncthreads();
+    lds_barrier();
     if (wm == 0 && lane < 32) {
 #pragma unroll
       for (int ni = 0; ni < kNI; ++ni) {
@@ -320,6 +321,56 @@ __device__ __forceinline__ void pull_tile(int idx, int mx, int nv, int xcd, int&
   n_tile = 8 * nwave + r2 % nsz;
 }
 
+// The tiles of a pulling workgroup as gemm_tiles walks them: claimed from the XCD's
+// counter by thread 0 when the tile before them starts, published at its end.
+struct PullTiles {
+  static constexpr bool kStream = true;
+  int32_t* counter;
+  int32_t* s_idx;       // LDS
+  void* smem;           // LDS scratch of the epilogue
+  int mx, nv, xcd;
+  int32_t total;
+  int32_t idx;          // the current tile's index; at the end the first one past `total`
+  int32_t claimed;
+  TileClock* clock;
+  int64_t* clk;
+  int64_t clk_slots;
+  int n_tiles;
+  int64_t slot;         // the current tile's record
+  uint64_t c0, r0;
+  int64_t prev_slot;
+
+  __device__ __forceinline__ void claim() {
+    if (threadIdx.x == 0) claimed = atomicAdd(counter, 1);
+  }
+  // The claimed index, for every thread.
+  __device__ __forceinline__ int32_t publish() {
+    if (threadIdx.x == 0) *s_idx = claimed;
+    lds_barrier();
+    const int32_t i = static_cast<int32_t>(uniform_u32(static_cast<uint32_t>(*s_idx)));
+    lds_barrier();  // every thread has read it
+    return i;
+  }
+  __device__ __forceinline__ void locate(int& mt, int& n_tile) {
+    pull_tile(idx, mx, nv, xcd, mt, n_tile);
+    slot = static_cast<int64_t>(mt) * n_tiles + n_tile;
+  }
+  __device__ __forceinline__ bool next(int& mt, int& n_tile) {
+    prev_slot = slot;
+    idx = publish();
+    if (idx >= total) return false;
+    locate(mt, n_tile);
+    return true;
+  }
+  __device__ __forceinline__ void* scratch() const { return smem; }
+  __device__ __forceinline__ void begin() {
+    c0 = clk ? __builtin_amdgcn_s_memtime() : 0;
+    r0 = clk ? __builtin_amdgcn_s_memrealtime() : 0;
+    clock->start(clk != nullptr);
+  }
+  __device__ __forceinline__ void end() { write_clock_record(clk, clk_slots, c0, r0, *clock, prev_slot); }
+};
+
 __global__ __launch_bounds__(256) void k_fill_i64(int64_t* p, int64_t n, int64_t v) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
@@ -342,6 +393,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
 void k_head_fwd_pull(GemmShape s, GemmShape st, float2* part, int64_t ldp, int32_t* next, int64_t* clk,
                      int64_t clk_slots) {
   __shared__ v4u lds[kStages][kStageChunks];
+  __shared__ float2 s_scratch[kBN];
   __shared__ int32_t s_idx;
   const int xcd = static_cast<int>(blockIdx.x & 7);
   const int64_t n_valid = s.n_dev ? static_cast<int64_t>(*s.n_dev) : s.n;
@@ -361,28 +413,24 @@ void k_head_fwd_pull(GemmShape s, GemmShape st, float2* part, int64_t ldp, int32
   epi_t.ldp = ldp;
   epi_t.M = st.m;
   epi_t.tile0 = s.m_tiles;
-  for (;;) {
-    if (threadIdx.x == 0) s_idx = atomicAdd(next + xcd, 1);
-    __syncthreads();  // also: the previous tile's epilogue is done with LDS
-    const int32_t idx = s_idx;
-    __syncthreads();  // every thread has read s_idx
-    if (idx >= total + tail) break;
-    if (idx >= total) {
-      const int n_tile = (idx - total) * 8 + xcd;
-      const uint64_t c0 = clk ? __builtin_amdgcn_s_memtime() : 0;
-      const uint64_t r0 = clk ? __builtin_amdgcn_s_memrealtime() : 0;
-      epi_t.clock.start(clk != nullptr);
-      gemm_tile<E, false, false>(st, epi_t, lds, 0, n_tile);
-      write_clock_record(clk, clk_slots, c0, r0, epi_t.clock, static_cast<int64_t>(s.m_tiles) * s.n_tiles + n_tile);
-      continue;
-    }
+  PullTiles tiles{next + xcd, &s_idx, s_scratch, mx, nv, xcd, total, 0, 0, &epi.clock, clk, clk_slots, s.n_tiles, 0, 0, 0, 0};
+  tiles.claim();
+  tiles.idx = tiles.publish();
+  if (tiles.idx < total) {
     int mt, n_tile;
-    pull_tile(idx, mx, nv, xcd, mt, n_tile);
+    tiles.locate(mt, n_tile);
+    gemm_tiles<E, false, false>(s, epi, lds, mt, n_tile, 0, tiles);
+  }
+  int32_t idx = tiles.idx;
+  while (idx < total + tail) {
+    const int n_tile = (idx - total) * 8 + xcd;
     const uint64_t c0 = clk ? __builtin_amdgcn_s_memtime() : 0;
     const uint64_t r0 = clk ? __builtin_amdgcn_s_memrealtime() : 0;
-    epi.clock.start(clk != nullptr);
-    gemm_tile<E, false, false>(s, epi, lds, mt, n_tile);
-    write_clock_record(clk, clk_slots, c0, r0, epi.clock, static_cast<int64_t>(mt) * s.n_tiles + n_tile);
+    epi_t.clock.start(clk != nullptr);
+    gemm_tile<E, false, false>(st, epi_t, lds, 0, n_tile);
+    write_clock_record(clk, clk_slots, c0, r0, epi_t.clock, static_cast<int64_t>(s.m_tiles) * s.n_tiles + n_tile);
+    tiles.claim();
+    idx = tiles.publish();
   }
 }
 
@@ -539,8 +587,7 @@ struct EpiDz {
   const float* lse_c;
   const int32_t* y_c;
   float gl[kNI], ll[kNI];
-  int64_t yl[kNI];
-  int yt[kNI];  // target row of the column's token inside the current tile, or -8 when outside
+  int yt[kNI];  // the column's target; in tile(), its row inside the tile, or -8 when outside
   TileClock clock;  // measurement hook
 
   __device__ __forceinline__ void mark(int phase) { clock.mark(phase); }
@@ -550,9 +597,15 @@ struct EpiDz {
     for (int ni = 0; ni < kNI; ++ni) {
       const int64_t c = n0 + acc_col(wn, ni, lane);
       gl[ni] = g_c[c];
-      ll[ni] = lse_c[c] * kLog2e;
-      yl[ni] = static_cast<int64_t>(y_c[c]) - v_base;
+      ll[ni] = lse_c[c];
+      yt[ni] = y_c[c];
     }
+  }
+  // begin()'s loads have arrived: placed before the next tile's copies are issued, so
+  // that no wait for them lies behind those.
+  __device__ __forceinline__ void settle() {
+#pragma unroll
+    for (int ni = 0; ni < kNI; ++ni) asm volatile("" : "+v"(gl[ni]), "+v"(ll[ni]), "+v"(yt[ni]));
   }
 
   // dz of accumulator (mi, ni, registers 4j .. 4j+3): four consecutive
@@ -589,7 +642,8 @@ struct EpiDz {
     const int rows = rows64 > kBM ? kBM : static_cast<int>(rows64);
 #pragma unroll
     for (int ni = 0; ni < kNI; ++ni) {
-      const int64_t y = yl[ni] - m0;
+      ll[ni] *= kLog2e;
+      const int64_t y = static_cast<int64_t>(yt[ni]) - v_base - m0;
       yt[ni] = y >= 0 && y < kBM ? static_cast<int>(y) : -8;
     }
     if constexpr (sizeof(typename E::storage) == 2) {
@@ -786,28 +840,26 @@ void k_bwd_dz_pull(GemmShape s, GemmShape st, EpiDz<E, false> epi, EpiDz<E, true
   const int mx = xcd < s.m_tiles ? (s.m_tiles - 1 - xcd) / 8 + 1 : 0;
   const int32_t total = mx * nv;
   const int32_t tail = st.m > 0 && xcd < nv ? (nv - 1 - xcd) / 8 + 1 : 0;
-  for (;;) {
-    if (threadIdx.x == 0) s_idx = atomicAdd(next + xcd, 1);
-    __syncthreads();  // also: the previous tile's epilogue is done with LDS
-    const int32_t idx = s_idx;
-    __syncthreads();  // every thread has read s_idx
-    if (idx >= total + tail) break;
+  PullTiles tiles{next + xcd, &s_idx, nullptr, mx, nv, xcd, total, 0, 0, &epi.clock, clk, clk_slots, s.n_tiles, 0, 0, 0, 0};
+  tiles.claim();
+  tiles.idx = tiles.publish();
+  if (tiles.idx < total) {
+    int mt, n_tile;
+    tiles.locate(mt, n_tile);
+    gemm_tiles<E, false, false>(s, epi, lds, mt, n_tile, 0, tiles);
+  }
+  int32_t idx = tiles.idx;
+  while (idx < total + tail) {
+    const int n_tile = (idx - total) * 8 + xcd;
     const uint64_t c0 = clk ? __builtin_amdgcn_s_memtime() : 0;
     const uint64_t r0 = clk ? __builtin_amdgcn_s_memrealtime() : 0;
-    if (idx >= total) {
-      const int n_tile = (idx - total) * 8 + xcd;
-      epi_t.clock.start(clk != nullptr);
-      gemm_tile<E, false, false>(st, epi_t, lds, 0, n_tile);
-      // the record names the tile within the block, not within the tail's own shape
-      if (epi_t.clock.tile_id >= 0) epi_t.clock.tile_id += static_cast<int64_t>(s.m_tiles) << 32;
-      write_clock_record(clk, clk_slots, c0, r0, epi_t.clock, static_cast<int64_t>(s.m_tiles) * s.n_tiles + n_tile);
-      continue;
-    }
-    int mt, n_tile;
-    pull_tile(idx, mx, nv, xcd, mt, n_tile);
-    epi.clock.start(clk != nullptr);
-    gemm_tile<E, false, false>(s, epi, lds, mt, n_tile);
-    write_clock_record(clk, clk_slots, c0, r0, epi.clock, static_cast<int64_t>(mt) * s.n_tiles + n_tile);
+    epi_t.clock.start(clk != nullptr);
+    gemm_tile<E, false, false>(st, epi_t, lds, 0, n_tile);
+    // the record names the tile within the block, not within the tail's own shape
+    if (epi_t.clock.tile_id >= 0) epi_t.clock.tile_id += static_cast<int64_t>(s.m_tiles) << 32;
+    write_clock_record(clk, clk_slots, c0, r0, epi_t.clock, static_cast<int64_t>(s.m_tiles) * s.n_tiles + n_tile);
+    tiles.claim();
+    idx = tiles.publish();
   }
 }
 
@@ -1104,7 +1156,7 @@ static hipError_t backward_impl(const void* hidden, int64_t ld_hidden, const voi
         sa.msplit = 1;
         sa.sn = pick_sn_msplit(sa.n_tiles);
       }
-      EpiDz<E, false> ez{dz, L.vc, full_v, v0, g_c, lse_c, y_c, {}, {}, {}, {}, {}};
+      EpiDz<E, false> ez{dz, L.vc, full_v, v0, g_c, lse_c, y_c, {}, {}, {}, {}};
       int64_t* clk = clocks(vb, SAO_KERNEL_BACKWARD_DZ);
       hook(vb, SAO_KERNEL_BACKWARD_DZ, false);
       if (sa.n_tiles <= kPullMaxNTiles) {
@@ -1115,7 +1167,7 @@ static hipError_t backward_impl(const void* hidden, int64_t ld_hidden, const voi
         if (vlen > full_v) {
           stail = make_shape(w + (v0 + full_v) * ld_w, ld_w, vlen - full_v, hg, H, T, H);
           stail.n_dev = count;
-          ezt = EpiDz<E, true>{dz + full_v, L.vc, vlen - full_v, v0 + full_v, g_c, lse_c, y_c, {}, {}, {}, {}, {}};
+          ezt = EpiDz<E, true>{dz + full_v, L.vc, vlen - full_v, v0 + full_v, g_c, lse_c, y_c, {}, {}, {}, {}};
         }
         if (clk) hipLaunchKernelGGL(k_fill_i64, dim3(64), dim3(256), 0, st, clk, 8 * tm.clock_slots, int64_t{0});
         hipLaunchKernelGGL(k_bwd_dz_pull<E>, dim3(static_cast<unsigned>(pull_grid())), dim3(kThreads), 0, st, sa,
@@ -1130,7 +1182,7 @@ static hipError_t backward_impl(const void* hidden, int64_t ld_hidden, const voi
     if (vlen > full_v && !tail_done) {
       GemmShape sa = make_shape(w + (v0 + full_v) * ld_w, ld_w, vlen - full_v, hg, H, T, H);
       sa.n_dev = count;
-      EpiDz<E, true> ez{dz + full_v, L.vc, vlen - full_v, v0 + full_v, g_c, lse_c, y_c, {}, {}, {}, {}, {}};
+      EpiDz<E, true> ez{dz + full_v, L.vc, vlen - full_v, v0 + full_v, g_c, lse_c, y_c, {}, {}, {}, {}};
       hipLaunchKernelGGL((k_bwd_dz<E, true>), dim3(gemm_grid(sa)), dim3(kThreads), 0, st, sa, ez,
                          static_cast<int64_t*>(nullptr), int64_t{0});
     }
