@@ -265,6 +265,11 @@ sao_status_t sao_clipped_loss(const float* logp, const float* logp_rollout, cons
                               const uint8_t* mask, int64_t T, float eps_low, float eps_high,
                               const int64_t* n_tokens, double* loss, float* g, uint8_t* flags,
                               int64_t* counts, void* ws, size_t ws_bytes, hipStream_t stream);
+/* The same with loss and counts written rather than added to (T == 0 leaves them untouched). */
+sao_status_t sao_clipped_loss_store(const float* logp, const float* logp_rollout, const float* adv,
+                                    const uint8_t* mask, int64_t T, float eps_low, float eps_high,
+                                    const int64_t* n_tokens, double* loss, float* g, uint8_t* flags,
+                                    int64_t* counts, void* ws, size_t ws_bytes, hipStream_t stream);
 
 /*
  * sao_clipped_loss without a workspace argument, for callers that cannot
@@ -272,7 +277,7 @@ sao_status_t sao_clipped_loss(const float* logp, const float* logp_rollout, cons
  * harnesses that forbid allocation). Same arguments, outputs, accumulation and
  * results as sao_clipped_loss (the same kernels; bit-identical outputs), minus
  * ws and ws_bytes. The kernels' scratch (per-block partials and the mask count)
- * is a static array of 114,944 bytes in device memory, one per GPU, which the
+ * is a static array of 131,072 bytes in device memory, one per GPU, which the
  * library obtains on its first call on each device (with that device current)
  * and holds until the process ends; no call allocates or frees anything. That
  * maximum covers every T, since the loss uses at most 2048 blocks of partials;
@@ -312,6 +317,12 @@ sao_status_t sao_ppo_loss(const float* logp, const float* logp_old, const float*
                           float eps_high, const int64_t* n_tokens, double* loss, float* g,
                           uint8_t* flags, int64_t* counts, void* ws, size_t ws_bytes,
                           hipStream_t stream);
+/* The same with loss and counts written rather than added to (T == 0 leaves them untouched). */
+sao_status_t sao_ppo_loss_store(const float* logp, const float* logp_old, const float* logp_behav,
+                                const float* adv, const uint8_t* mask, int64_t T, float eps_low,
+                                float eps_high, const int64_t* n_tokens, double* loss, float* g,
+                                uint8_t* flags, int64_t* counts, void* ws, size_t ws_bytes,
+                                hipStream_t stream);
 
 /*
  * Explained variance of the critic, Sec. 4.4, over tokens with mask 1:
@@ -328,6 +339,11 @@ sao_status_t sao_ppo_loss(const float* logp, const float* logp_old, const float*
 sao_status_t sao_explained_variance(const float* values, const float* ret, const uint8_t* mask,
                                     int64_t T, double* moments, double* ev, void* ws,
                                     size_t ws_bytes, hipStream_t stream);
+/* The same with moments written from this call's tokens alone (T == 0 leaves them untouched). */
+sao_status_t sao_explained_variance_store(const float* values, const float* ret,
+                                          const uint8_t* mask, int64_t T, double* moments,
+                                          double* ev, void* ws, size_t ws_bytes,
+                                          hipStream_t stream);
 
 /*
  * Backward of the DIS loss through the log-softmax of Eq. (1)-(2):
@@ -382,6 +398,12 @@ sao_status_t sao_value_loss(const void* hidden, int64_t ld_hidden, const void* w
                             const int64_t* n_tokens, sao_dtype_t dtype, double* loss_v,
                             void* dhidden_v, float* dw_v, void* ws, size_t ws_bytes,
                             hipStream_t stream);
+/* The same with loss_v and dw_v written rather than added to (T == 0 leaves them untouched). */
+sao_status_t sao_value_loss_store(const void* hidden, int64_t ld_hidden, const void* w_v,
+                                  const float* v, const float* ret, const uint8_t* mask, int64_t T,
+                                  int64_t H, const int64_t* n_tokens, sao_dtype_t dtype,
+                                  double* loss_v, void* dhidden_v, float* dw_v, void* ws,
+                                  size_t ws_bytes, hipStream_t stream);
 
 /*
  * Measurement hook, not part of the pass. For the calling thread, records the

@@ -25,6 +25,7 @@ FLAG_MASKED, FLAG_USED, FLAG_LOW, FLAG_HIGH, FLAG_NONFINITE = 0, 1, 2, 3, 4
 EXPORTS = ("sao_status_string", "sao_last_error_message", "sao_version", "sao_workspace_size",
            "sao_token_logprob", "sao_advantage", "sao_clipped_loss", "sao_loss_backward", "sao_loss_backward_store",
            "sao_value_forward", "sao_value_loss", "sao_ppo_loss", "sao_explained_variance", "sao_step_advantage",
+           "sao_clipped_loss_store", "sao_ppo_loss_store", "sao_explained_variance_store", "sao_value_loss_store",
            "sao_group_advantage", "sao_running_mean_advantage", "sao_clipped_loss_noalloc",
            "sao_debug_time_kernel", "sao_debug_clock_samples")
 KERNEL_NONE, KERNEL_HEAD_FORWARD, KERNEL_BACKWARD_DZ, KERNEL_BACKWARD_DH, KERNEL_BACKWARD_DW = 0, 1, 2, 3, 4
@@ -54,8 +55,6 @@ _SIGS = {
                                                 _p, _p, _p, _p]),
     "sao_loss_backward": (ctypes.c_int, [_p, _i64, _p, _i64, _p, _p, _p, _i64, _i64, _i64,
                                          ctypes.c_int, _p, _p, _p, ctypes.c_size_t, _p]),
-    "sao_loss_backward_store": (ctypes.c_int, [_p, _i64, _p, _i64, _p, _p, _p, _i64, _i64, _i64,
-                                               ctypes.c_int, _p, _p, _p, ctypes.c_size_t, _p]),
     "sao_value_forward": (ctypes.c_int, [_p, _i64, _p, _i64, _i64, ctypes.c_int, _p, _p, ctypes.c_size_t, _p]),
     "sao_value_loss": (ctypes.c_int, [_p, _i64, _p, _p, _p, _p, _i64, _i64, _p, ctypes.c_int, _p, _p, _p, _p,
                                       ctypes.c_size_t, _p]),
@@ -73,6 +72,9 @@ _SIGS = {
     "sao_debug_time_kernel": (None, [ctypes.c_int, _p, _p]),
     "sao_debug_clock_samples": (None, [ctypes.c_int, _p, _i64]),
 }
+
+for _name in ("sao_clipped_loss", "sao_ppo_loss", "sao_explained_variance", "sao_value_loss", "sao_loss_backward"):
+    _SIGS[_name + "_store"] = _SIGS[_name]
 
 _lib = None
 
@@ -146,6 +148,11 @@ def _workspace(nbytes: int, device) -> Optional[torch.Tensor]:
     return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
+def _fresh(T: int, n: int, dtype: torch.dtype, device) -> torch.Tensor:
+    """n elements that a call on T tokens writes whole; zeros when it does not run (T == 0)."""
+    return (torch.empty if T else torch.zeros)(n, dtype=dtype, device=device)
+
+
 def _head_shapes(hidden: torch.Tensor, w_head: torch.Tensor) -> None:
     if hidden.dim() != 2 or w_head.dim() != 2 or w_head.shape[1] != hidden.shape[1]:
         raise ValueError("hidden [T, H] and w_head [V, H] must share H")
@@ -194,7 +201,7 @@ def advantage(values: torch.Tensor, rewards: torch.Tensor, mask: torch.Tensor, c
     _vec(status, "status", torch.int32, 1, dev, optional=True)
     adv = torch.empty(T, dtype=torch.float32, device=dev)
     ret = torch.empty(T, dtype=torch.float32, device=dev)
-    n_tok = torch.zeros(1, dtype=torch.int64, device=dev) if want_count else None
+    n_tok = _fresh(T, 1, torch.int64, dev) if want_count else None
     ws = _workspace(workspace_size(OP_ADVANTAGE, T, 1, 1, SAO_F32), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
         _check(lib().sao_advantage(
@@ -222,7 +229,7 @@ def step_advantage(values: torch.Tensor, rewards: torch.Tensor, mask: torch.Tens
     adv = torch.empty(T, dtype=torch.float32, device=dev)
     ret = torch.empty(T, dtype=torch.float32, device=dev)
     last = torch.empty(T, dtype=torch.uint8, device=dev) if want_last else None
-    n_tok = torch.zeros(1, dtype=torch.int64, device=dev) if want_count else None
+    n_tok = _fresh(T, 1, torch.int64, dev) if want_count else None
     ws = _workspace(workspace_size(OP_STEP_ADVANTAGE, T, 1, 1, SAO_F32), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
         _check(lib().sao_step_advantage(
@@ -250,7 +257,7 @@ def group_advantage(rewards: torch.Tensor, mask: torch.Tensor, cu_seqlens: torch
     adv = torch.empty(T, dtype=torch.float32, device=dev)
     traj_reward = torch.empty(B, dtype=torch.float64, device=dev)
     traj_adv = torch.empty(B, dtype=torch.float64, device=dev)
-    n_tok = torch.zeros(1, dtype=torch.int64, device=dev) if want_count else None
+    n_tok = _fresh(T, 1, torch.int64, dev) if want_count else None
     ws = _workspace(workspace_size(OP_GROUP_ADVANTAGE, T, 1, 1, SAO_F32), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
         _check(lib().sao_group_advantage(
@@ -281,7 +288,7 @@ def running_mean_advantage(rewards: torch.Tensor, mask: torch.Tensor, cu_seqlens
     adv = torch.empty(T, dtype=torch.float32, device=dev)
     traj_reward = torch.empty(B, dtype=torch.float64, device=dev)
     traj_adv = torch.empty(B, dtype=torch.float64, device=dev)
-    n_tok = torch.zeros(1, dtype=torch.int64, device=dev) if want_count else None
+    n_tok = _fresh(T, 1, torch.int64, dev) if want_count else None
     ws = _workspace(workspace_size(OP_RUNNING_MEAN_ADVANTAGE, T, 1, 1, SAO_F32), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
         _check(lib().sao_running_mean_advantage(
@@ -294,7 +301,7 @@ def running_mean_advantage(rewards: torch.Tensor, mask: torch.Tensor, cu_seqlens
 def clipped_loss(logp: torch.Tensor, logp_rollout: torch.Tensor, adv: torch.Tensor, mask: torch.Tensor,
                  eps_low: float, eps_high: float, n_tokens: Optional[torch.Tensor] = None,
                  loss: Optional[torch.Tensor] = None, counts: Optional[torch.Tensor] = None):
-    """DIS loss: (loss[2] f64 +=, g, flags, counts[5] i64 +=). Zeroed accumulators are made if not given."""
+    """DIS loss: (loss[2] f64 +=, g, flags, counts[5] i64 +=). Accumulators start from zero if not given."""
     T = logp.shape[0]
     dev = logp.device
     _vec(logp, "logp", torch.float32, T, dev)
@@ -302,9 +309,12 @@ def clipped_loss(logp: torch.Tensor, logp_rollout: torch.Tensor, adv: torch.Tens
     _vec(adv, "adv", torch.float32, T, dev)
     _vec(mask, "mask", torch.uint8, T, dev)
     _vec(n_tokens, "n_tokens", torch.int64, 1, dev, optional=True)
-    if loss is None:
+    store = loss is None and counts is None  # both start with this call
+    if store:
+        loss, counts = _fresh(T, 2, torch.float64, dev), _fresh(T, 5, torch.int64, dev)
+    elif loss is None:
         loss = torch.zeros(2, dtype=torch.float64, device=dev)
-    if counts is None:
+    elif counts is None:
         counts = torch.zeros(5, dtype=torch.int64, device=dev)
     _vec(loss, "loss", torch.float64, 2, dev)
     _vec(counts, "counts", torch.int64, 5, dev)
@@ -312,7 +322,7 @@ def clipped_loss(logp: torch.Tensor, logp_rollout: torch.Tensor, adv: torch.Tens
     flags = torch.empty(T, dtype=torch.uint8, device=dev)
     ws = _workspace(workspace_size(OP_LOSS, T, 1, 1, SAO_F32), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
-        _check(lib().sao_clipped_loss(
+        _check((lib().sao_clipped_loss_store if store else lib().sao_clipped_loss)(
             _ptr(logp), _ptr(logp_rollout), _ptr(adv), _ptr(mask), T, float(eps_low), float(eps_high),
             _ptr(n_tokens), _ptr(loss), _ptr(g), _ptr(flags), _ptr(counts), _ptr(ws),
             0 if ws is None else ws.numel(), _stream(dev)))
@@ -351,7 +361,7 @@ def ppo_loss(logp: torch.Tensor, logp_old: torch.Tensor, adv: torch.Tensor, mask
              logp_behav: Optional[torch.Tensor] = None, loss: Optional[torch.Tensor] = None,
              counts: Optional[torch.Tensor] = None):
     """Clipped surrogate (standard, clip-higher, or decoupled with logp_behav):
-    (loss[1] f64 +=, g, flags, counts[5] i64 +=). Zeroed accumulators are made if not given."""
+    (loss[1] f64 +=, g, flags, counts[5] i64 +=). Accumulators start from zero if not given."""
     T = logp.shape[0]
     dev = logp.device
     _vec(logp, "logp", torch.float32, T, dev)
@@ -360,9 +370,12 @@ def ppo_loss(logp: torch.Tensor, logp_old: torch.Tensor, adv: torch.Tensor, mask
     _vec(adv, "adv", torch.float32, T, dev)
     _vec(mask, "mask", torch.uint8, T, dev)
     _vec(n_tokens, "n_tokens", torch.int64, 1, dev, optional=True)
-    if loss is None:
+    store = loss is None and counts is None  # both start with this call
+    if store:
+        loss, counts = _fresh(T, 1, torch.float64, dev), _fresh(T, 5, torch.int64, dev)
+    elif loss is None:
         loss = torch.zeros(1, dtype=torch.float64, device=dev)
-    if counts is None:
+    elif counts is None:
         counts = torch.zeros(5, dtype=torch.int64, device=dev)
     _vec(loss, "loss", torch.float64, 1, dev)
     _vec(counts, "counts", torch.int64, 5, dev)
@@ -370,7 +383,7 @@ def ppo_loss(logp: torch.Tensor, logp_old: torch.Tensor, adv: torch.Tensor, mask
     flags = torch.empty(T, dtype=torch.uint8, device=dev)
     ws = _workspace(workspace_size(OP_PPO_LOSS, T, 1, 1, SAO_F32), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
-        _check(lib().sao_ppo_loss(
+        _check((lib().sao_ppo_loss_store if store else lib().sao_ppo_loss)(
             _ptr(logp), _ptr(logp_old), _ptr(logp_behav), _ptr(adv), _ptr(mask), T, float(eps_low), float(eps_high),
             _ptr(n_tokens), _ptr(loss), _ptr(g), _ptr(flags), _ptr(counts), _ptr(ws),
             0 if ws is None else ws.numel(), _stream(dev)))
@@ -380,19 +393,22 @@ def ppo_loss(logp: torch.Tensor, logp_old: torch.Tensor, adv: torch.Tensor, mask
 def explained_variance(values: torch.Tensor, ret: torch.Tensor, mask: torch.Tensor,
                        moments: Optional[torch.Tensor] = None):
     """(ev [1] f64, moments [5] f64): EV = 1 - Var(R - V) / Var(R) over mask tokens, with this
-    call's tokens combined into `moments` (zeroed if not given) so chunked calls cover a batch."""
+    call's tokens combined into `moments` (which start from zero if not given) so chunked calls cover a batch."""
     T = values.shape[0]
     dev = values.device
     _vec(values, "values", torch.float32, T, dev)
     _vec(ret, "ret", torch.float32, T, dev)
     _vec(mask, "mask", torch.uint8, T, dev)
-    if moments is None:
-        moments = torch.zeros(5, dtype=torch.float64, device=dev)
+    store = moments is None
+    if store:
+        moments = _fresh(T, 5, torch.float64, dev)
     _vec(moments, "moments", torch.float64, 5, dev)
-    ev = torch.full((1,), float("nan"), dtype=torch.float64, device=dev)
+    ev = torch.empty(1, dtype=torch.float64, device=dev)
+    if T == 0:
+        ev.fill_(float("nan"))
     ws = _workspace(workspace_size(OP_EXPLAINED_VARIANCE, T, 1, 1, SAO_F32), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
-        _check(lib().sao_explained_variance(
+        _check((lib().sao_explained_variance_store if store else lib().sao_explained_variance)(
             _ptr(values), _ptr(ret), _ptr(mask), T, _ptr(moments), _ptr(ev), _ptr(ws),
             0 if ws is None else ws.numel(), _stream(dev)))
     return ev, moments
@@ -455,9 +471,12 @@ def value_loss(hidden: torch.Tensor, w_value: torch.Tensor, v: torch.Tensor, ret
     _vec(ret, "ret", torch.float32, T, dev)
     _vec(mask, "mask", torch.uint8, T, dev)
     _vec(n_tokens, "n_tokens", torch.int64, 1, dev, optional=True)
-    if loss is None:
+    store = loss is None and dw_value is None  # both start with this call
+    if store:
+        loss, dw_value = _fresh(T, 1, torch.float64, dev), _fresh(T, H, torch.float32, dev)
+    elif loss is None:
         loss = torch.zeros(1, dtype=torch.float64, device=dev)
-    if dw_value is None:
+    elif dw_value is None:
         dw_value = torch.zeros(H, dtype=torch.float32, device=dev)
     if dhidden is None:
         dhidden = torch.empty((T, H), dtype=hidden.dtype, device=dev)
@@ -466,7 +485,7 @@ def value_loss(hidden: torch.Tensor, w_value: torch.Tensor, v: torch.Tensor, ret
     _vec(dhidden, "dhidden", hidden.dtype, T * H, dev)
     ws = _workspace(workspace_size(OP_VALUE, T, H, 1, dt), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
-        _check(lib().sao_value_loss(
+        _check((lib().sao_value_loss_store if store else lib().sao_value_loss)(
             _ptr(hidden), _rows(hidden, "hidden"), _ptr(w_value), _ptr(v), _ptr(ret), _ptr(mask), T, H,
             _ptr(n_tokens), dt, _ptr(loss), _ptr(dhidden), _ptr(dw_value), _ptr(ws),
             0 if ws is None else ws.numel(), _stream(dev)))

@@ -102,6 +102,65 @@ sao_status_t backward(const char* name, const void* hidden, int64_t ld_hidden, c
                 name);
 }
 
+sao_status_t clipped_loss(const char* what, bool store, const float* logp, const float* logp_rollout,
+                          const float* adv, const uint8_t* mask, int64_t T, float eps_low, float eps_high,
+                          const int64_t* n_tokens, double* loss, float* g, uint8_t* flags, int64_t* counts,
+                          void* ws, size_t ws_bytes, hipStream_t stream) {
+  if (!logp || !logp_rollout || !adv || !mask || !loss || !g || !flags || !counts)
+    return fail(SAO_ERR_NULL, "logp, logp_rollout, adv, mask, loss, g, flags and counts are required");
+  if (T < 0 || T > kMaxRows) return fail(SAO_ERR_SHAPE, "T=%lld out of range", (long long)T);
+  if (!(eps_low >= 0.0f) || !std::isfinite(eps_low) || !(eps_high >= 0.0f) || !std::isfinite(eps_high))
+    return fail(SAO_ERR_VALUE, "eps_low=%g, eps_high=%g must be finite and >= 0", eps_low, eps_high);
+  if (T == 0) return ok();
+  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_LOSS, T, 1, 1, SAO_F32))) return s;
+  return device(sao::launch_loss(logp, logp_rollout, adv, mask, T, eps_low, eps_high, n_tokens, loss, g, flags,
+                                 counts, store, ws, stream),
+                what);
+}
+
+sao_status_t ppo_loss(const char* what, bool store, const float* logp, const float* logp_old,
+                      const float* logp_behav, const float* adv, const uint8_t* mask, int64_t T, float eps_low,
+                      float eps_high, const int64_t* n_tokens, double* loss, float* g, uint8_t* flags,
+                      int64_t* counts, void* ws, size_t ws_bytes, hipStream_t stream) {
+  if (!logp || !logp_old || !adv || !mask || !loss || !g || !flags || !counts)
+    return fail(SAO_ERR_NULL, "logp, logp_old, adv, mask, loss, g, flags and counts are required");
+  if (T < 0 || T > kMaxRows) return fail(SAO_ERR_SHAPE, "T=%lld out of range", (long long)T);
+  if (!(eps_low >= 0.0f) || !std::isfinite(eps_low) || !(eps_high >= 0.0f) || !std::isfinite(eps_high))
+    return fail(SAO_ERR_VALUE, "eps_low=%g, eps_high=%g must be finite and >= 0", eps_low, eps_high);
+  if (T == 0) return ok();
+  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_PPO_LOSS, T, 1, 1, SAO_F32))) return s;
+  return device(sao::launch_ppo_loss(logp, logp_old, logp_behav, adv, mask, T, eps_low, eps_high, n_tokens, loss,
+                                     g, flags, counts, store, ws, stream),
+                what);
+}
+
+sao_status_t explained_variance(const char* what, bool store, const float* values, const float* ret,
+                                const uint8_t* mask, int64_t T, double* moments, double* ev, void* ws,
+                                size_t ws_bytes, hipStream_t stream) {
+  if (!values || !ret || !mask || !moments) return fail(SAO_ERR_NULL, "values, ret, mask and moments are required");
+  if (T < 0 || T > kMaxRows) return fail(SAO_ERR_SHAPE, "T=%lld out of range", (long long)T);
+  if (T == 0) return ok();
+  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_EXPLAINED_VARIANCE, T, 1, 1, SAO_F32)))
+    return s;
+  return device(sao::launch_explained_variance(values, ret, mask, T, moments, ev, store, ws, stream),
+                what);
+}
+
+sao_status_t value_loss(const char* what, bool store, const void* hidden, int64_t ld_hidden, const void* w_v,
+                        const float* v, const float* ret, const uint8_t* mask, int64_t T, int64_t H,
+                        const int64_t* n_tokens, sao_dtype_t dtype, double* loss_v, void* dhidden_v, float* dw_v,
+                        void* ws, size_t ws_bytes, hipStream_t stream) {
+  if (!hidden || !w_v || !v || !ret || !mask || !loss_v || !dhidden_v || !dw_v)
+    return fail(SAO_ERR_NULL, "hidden, w_v, v, ret, mask, loss_v, dhidden_v and dw_v are required");
+  if (sao_status_t s = check_head(hidden, ld_hidden, w_v, H, T, H, 1, dtype)) return s;
+  if (!aligned16(dhidden_v)) return fail(SAO_ERR_SHAPE, "dhidden_v must be 16-byte aligned");
+  if (T == 0) return ok();
+  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_VALUE, T, H, 1, dtype))) return s;
+  return device(sao::launch_value_loss(hidden, ld_hidden, w_v, v, ret, mask, T, H, n_tokens, dtype == SAO_BF16,
+                                       loss_v, dhidden_v, dw_v, store, ws, stream),
+                what);
+}
+
 }  // namespace
 
 extern "C" {
@@ -211,9 +270,11 @@ sao_status_t sao_group_advantage(const float* rewards, const uint8_t* mask, cons
   if (!traj_reward || !traj_adv) return fail(SAO_ERR_NULL, "traj_reward and traj_adv are required");
   if (group_size < 1 || B % group_size != 0)
     return fail(SAO_ERR_SHAPE, "B=%d must be a positive multiple of group_size=%d", (int)B, (int)group_size);
-  if (!(eps_stab >= 0.0) || !std::isfinite(eps_stab)) return fail(SAO_ERR_VALUE, "eps_stab must be finite and >= 0");
+  if (!(eps_stab >= 0.0) || !std::isfinite(eps_stab)) return fail(SAO_ERR_VALUE,
+      "eps_stab must be finite and >= 0");
   if (T == 0) return ok();
-  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_GROUP_ADVANTAGE, T, 1, 1, SAO_F32))) return s;
+  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_GROUP_ADVANTAGE, T, 1, 1,
+      SAO_F32))) return s;
   return device(sao::launch_group_advantage(rewards, mask, cu_seqlens, B, T, group_size, eps_stab, adv, traj_reward,
                                             traj_adv, n_tokens, status, ws, stream),
                 "sao_group_advantage launch");
@@ -237,20 +298,20 @@ sao_status_t sao_running_mean_advantage(const float* rewards, const uint8_t* mas
                 "sao_running_mean_advantage launch");
 }
 
-sao_status_t sao_clipped_loss(const float* logp, const float* logp_rollout, const float* adv,
-                              const uint8_t* mask, int64_t T, float eps_low, float eps_high,
-                              const int64_t* n_tokens, double* loss, float* g, uint8_t* flags, int64_t* counts,
-                              void* ws, size_t ws_bytes, hipStream_t stream) {
-  if (!logp || !logp_rollout || !adv || !mask || !loss || !g || !flags || !counts)
-    return fail(SAO_ERR_NULL, "logp, logp_rollout, adv, mask, loss, g, flags and counts are required");
-  if (T < 0 || T > kMaxRows) return fail(SAO_ERR_SHAPE, "T=%lld out of range", (long long)T);
-  if (!(eps_low >= 0.0f) || !std::isfinite(eps_low) || !(eps_high >= 0.0f) || !std::isfinite(eps_high))
-    return fail(SAO_ERR_VALUE, "eps_low=%g, eps_high=%g must be finite and >= 0", eps_low, eps_high);
-  if (T == 0) return ok();
-  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_LOSS, T, 1, 1, SAO_F32))) return s;
-  return device(sao::launch_loss(logp, logp_rollout, adv, mask, T, eps_low, eps_high, n_tokens, loss, g, flags,
-                                 counts, ws, stream),
-                "sao_clipped_loss launch");
+sao_status_t sao_clipped_loss(const float* logp, const float* logp_rollout, const float* adv, const uint8_t* mask,
+                              int64_t T, float eps_low, float eps_high, const int64_t* n_tokens, double* loss,
+                              float* g, uint8_t* flags, int64_t* counts, void* ws, size_t ws_bytes,
+                              hipStream_t stream) {
+  return clipped_loss("sao_clipped_loss launch", false, logp, logp_rollout, adv, mask, T, eps_low, eps_high,
+                      n_tokens, loss, g, flags, counts, ws, ws_bytes, stream);
+}
+
+sao_status_t sao_clipped_loss_store(const float* logp, const float* logp_rollout, const float* adv,
+                                    const uint8_t* mask, int64_t T, float eps_low, float eps_high,
+                                    const int64_t* n_tokens, double* loss, float* g, uint8_t* flags,
+                                    int64_t* counts, void* ws, size_t ws_bytes, hipStream_t stream) {
+  return clipped_loss("sao_clipped_loss_store launch", true, logp, logp_rollout, adv, mask, T, eps_low, eps_high,
+                      n_tokens, loss, g, flags, counts, ws, ws_bytes, stream);
 }
 
 sao_status_t sao_clipped_loss_noalloc(const float* logp, const float* logp_rollout, const float* adv,
@@ -276,34 +337,37 @@ sao_status_t sao_ppo_loss(const float* logp, const float* logp_old, const float*
                           const uint8_t* mask, int64_t T, float eps_low, float eps_high, const int64_t* n_tokens,
                           double* loss, float* g, uint8_t* flags, int64_t* counts, void* ws, size_t ws_bytes,
                           hipStream_t stream) {
-  if (!logp || !logp_old || !adv || !mask || !loss || !g || !flags || !counts)
-    return fail(SAO_ERR_NULL, "logp, logp_old, adv, mask, loss, g, flags and counts are required");
-  if (T < 0 || T > kMaxRows) return fail(SAO_ERR_SHAPE, "T=%lld out of range", (long long)T);
-  if (!(eps_low >= 0.0f) || !std::isfinite(eps_low) || !(eps_high >= 0.0f) || !std::isfinite(eps_high))
-    return fail(SAO_ERR_VALUE, "eps_low=%g, eps_high=%g must be finite and >= 0", eps_low, eps_high);
-  if (T == 0) return ok();
-  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_PPO_LOSS, T, 1, 1, SAO_F32))) return s;
-  return device(sao::launch_ppo_loss(logp, logp_old, logp_behav, adv, mask, T, eps_low, eps_high, n_tokens, loss,
-                                     g, flags, counts, ws, stream),
-                "sao_ppo_loss launch");
+  return ppo_loss("sao_ppo_loss launch", false, logp, logp_old, logp_behav, adv, mask, T, eps_low, eps_high,
+                  n_tokens, loss, g, flags, counts, ws, ws_bytes, stream);
+}
+
+sao_status_t sao_ppo_loss_store(const float* logp, const float* logp_old, const float* logp_behav, const float* adv,
+                                const uint8_t* mask, int64_t T, float eps_low, float eps_high,
+                                const int64_t* n_tokens, double* loss, float* g, uint8_t* flags, int64_t* counts,
+                                void* ws, size_t ws_bytes, hipStream_t stream) {
+  return ppo_loss("sao_ppo_loss_store launch", true, logp, logp_old, logp_behav, adv, mask, T, eps_low, eps_high,
+                  n_tokens, loss, g, flags, counts, ws, ws_bytes, stream);
 }
 
 sao_status_t sao_explained_variance(const float* values, const float* ret, const uint8_t* mask, int64_t T,
                                     double* moments, double* ev, void* ws, size_t ws_bytes, hipStream_t stream) {
-  if (!values || !ret || !mask || !moments) return fail(SAO_ERR_NULL, "values, ret, mask and moments are required");
-  if (T < 0 || T > kMaxRows) return fail(SAO_ERR_SHAPE, "T=%lld out of range", (long long)T);
-  if (T == 0) return ok();
-  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_EXPLAINED_VARIANCE, T, 1, 1, SAO_F32)))
-    return s;
-  return device(sao::launch_explained_variance(values, ret, mask, T, moments, ev, ws, stream),
-                "sao_explained_variance launch");
+  return explained_variance("sao_explained_variance launch", false, values, ret, mask, T, moments, ev, ws, ws_bytes,
+                            stream);
+}
+
+sao_status_t sao_explained_variance_store(const float* values, const float* ret, const uint8_t* mask, int64_t T,
+                                          double* moments, double* ev, void* ws, size_t ws_bytes,
+                                          hipStream_t stream) {
+  return explained_variance("sao_explained_variance_store launch", true, values, ret, mask, T, moments, ev, ws,
+                            ws_bytes, stream);
 }
 
 sao_status_t sao_loss_backward(const void* hidden, int64_t ld_hidden, const void* w_head, int64_t ld_w,
                                const int32_t* target, const float* lse, const float* g, int64_t T, int64_t H,
                                int64_t V, sao_dtype_t dtype, void* dhidden, float* dw_head, void* ws,
                                size_t ws_bytes, hipStream_t stream) {
-  return backward("sao_loss_backward launch", hidden, ld_hidden, w_head, ld_w, target, lse, g, T, H, V, dtype, dhidden,
+  return backward("sao_loss_backward launch", hidden, ld_hidden, w_head, ld_w, target, lse, g, T, H, V, dtype,
+                  dhidden,
                   dw_head, false, ws, ws_bytes, stream);
 }
 
@@ -330,15 +394,16 @@ sao_status_t sao_value_loss(const void* hidden, int64_t ld_hidden, const void* w
                             const float* ret, const uint8_t* mask, int64_t T, int64_t H, const int64_t* n_tokens,
                             sao_dtype_t dtype, double* loss_v, void* dhidden_v, float* dw_v, void* ws,
                             size_t ws_bytes, hipStream_t stream) {
-  if (!hidden || !w_v || !v || !ret || !mask || !loss_v || !dhidden_v || !dw_v)
-    return fail(SAO_ERR_NULL, "hidden, w_v, v, ret, mask, loss_v, dhidden_v and dw_v are required");
-  if (sao_status_t s = check_head(hidden, ld_hidden, w_v, H, T, H, 1, dtype)) return s;
-  if (!aligned16(dhidden_v)) return fail(SAO_ERR_SHAPE, "dhidden_v must be 16-byte aligned");
-  if (T == 0) return ok();
-  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_VALUE, T, H, 1, dtype))) return s;
-  return device(sao::launch_value_loss(hidden, ld_hidden, w_v, v, ret, mask, T, H, n_tokens, dtype == SAO_BF16,
-                                       loss_v, dhidden_v, dw_v, ws, stream),
-                "sao_value_loss launch");
+  return value_loss("sao_value_loss launch", false, hidden, ld_hidden, w_v, v, ret, mask, T, H, n_tokens, dtype,
+                    loss_v, dhidden_v, dw_v, ws, ws_bytes, stream);
+}
+
+sao_status_t sao_value_loss_store(const void* hidden, int64_t ld_hidden, const void* w_v, const float* v,
+                                  const float* ret, const uint8_t* mask, int64_t T, int64_t H,
+                                  const int64_t* n_tokens, sao_dtype_t dtype, double* loss_v, void* dhidden_v,
+                                  float* dw_v, void* ws, size_t ws_bytes, hipStream_t stream) {
+  return value_loss("sao_value_loss_store launch", true, hidden, ld_hidden, w_v, v, ret, mask, T, H, n_tokens,
+                    dtype, loss_v, dhidden_v, dw_v, ws, ws_bytes, stream);
 }
 
 }  // extern "C"

@@ -78,10 +78,11 @@ struct ShiftedSums {
   }
 };
 
+template <int QUADS>
 __global__ __launch_bounds__(kLossThreads) void k_ev(const float* values, const float* ret, const uint8_t* mask,
                                                      int64_t T, Moments* part, bool vec_ok) {
   ShiftedSums acc;
-  walk_tokens<kLossThreads>(
+  walk_tokens<kLossThreads, QUADS>(
       T, vec_ok,
       [&](int64_t t) {
         const f32x4_t v4 = *reinterpret_cast<const f32x4_t*>(values + t);
@@ -99,16 +100,15 @@ __global__ __launch_bounds__(kLossThreads) void k_ev(const float* values, const 
 }
 
 // Combines the block partials (thread i takes blocks i, i + THREADS, ... in
-// order), then the caller's running moments first and this call's second; writes
-// them back and, when asked, EV from them.
-__global__ __launch_bounds__(kLossThreads) void k_ev_final(const Moments* part, int nblk, double* state,
+// order), then the caller's running moments first and this call's second (with
+// `store` this call's alone); writes them back and, when asked, EV from them.
+__global__ __launch_bounds__(kLossThreads) void k_ev_final(const Moments* part, int nblk, bool store, double* state,
                                                            double* ev) {
   Moments m{0.0, 0.0, 0.0, 0.0, 0.0};
   for (int i = threadIdx.x; i < nblk; i += kLossThreads) m = combine(m, part[i]);
   m = block_combine<kLossThreads>(m);
   if (threadIdx.x == 0) {
-    const Moments s{state[0], state[1], state[2], state[3], state[4]};
-    m = combine(s, m);
+    if (!store) m = combine(Moments{state[0], state[1], state[2], state[3], state[4]}, m);
     state[0] = m.n;
     state[1] = m.mr;
     state[2] = m.m2r;
@@ -119,14 +119,16 @@ __global__ __launch_bounds__(kLossThreads) void k_ev_final(const Moments* part, 
 }
 
 int launch_explained_variance(const float* values, const float* ret, const uint8_t* mask, int64_t T,
-                                     double* moments, double* ev, void* ws, hipStream_t st) {
+                                     double* moments, double* ev, bool store, void* ws, hipStream_t st) {
   const EvLayout L = ev_layout(T);
   Moments* part = reinterpret_cast<Moments*>(static_cast<char*>(ws) + L.part);
   const int nblk = static_cast<int>(L.blocks);
   const bool vec_ok = ((reinterpret_cast<uintptr_t>(values) | reinterpret_cast<uintptr_t>(ret)) & 15u) == 0 &&
                       (reinterpret_cast<uintptr_t>(mask) & 3u) == 0;
-  hipLaunchKernelGGL(k_ev, dim3(nblk), dim3(kLossThreads), 0, st, values, ret, mask, T, part, vec_ok);
-  hipLaunchKernelGGL(k_ev_final, dim3(1), dim3(kLossThreads), 0, st, part, nblk, moments, ev);
+  const auto kernel = T <= kLossOneQuadTokens ? k_ev<1> : k_ev<2>;
+  hipLaunchKernelGGL(kernel, dim3(nblk), dim3(kLossThreads), 0, st, values, ret, mask, T, part, vec_ok);
+  hipLaunchKernelGGL(k_ev_final, dim3(1), dim3(kLossThreads), 0, st, part, nblk, store, moments,
+                     ev);
   return hipGetLastError();
 }
 

@@ -41,7 +41,7 @@ int launch_running_mean_advantage(const float*, const uint8_t*, const int32_t*, 
   return kNoDevice;
 }
 int launch_loss(const float*, const float*, const float*, const uint8_t*, int64_t, float, float, const int64_t*,
-                double*, float*, uint8_t*, int64_t*, void*, hipStream_t) {
+                double*, float*, uint8_t*, int64_t*, bool, void*, hipStream_t) {
   return kNoDevice;
 }
 int launch_loss_noalloc(const float*, const float*, const float*, const uint8_t*, int64_t, float, float,
@@ -49,10 +49,10 @@ int launch_loss_noalloc(const float*, const float*, const float*, const uint8_t*
   return kNoDevice;
 }
 int launch_ppo_loss(const float*, const float*, const float*, const float*, const uint8_t*, int64_t, float, float,
-                    const int64_t*, double*, float*, uint8_t*, int64_t*, void*, hipStream_t) {
+                    const int64_t*, double*, float*, uint8_t*, int64_t*, bool, void*, hipStream_t) {
   return kNoDevice;
 }
-int launch_explained_variance(const float*, const float*, const uint8_t*, int64_t, double*, double*, void*,
+int launch_explained_variance(const float*, const float*, const uint8_t*, int64_t, double*, double*, bool, void*,
                               hipStream_t) {
   return kNoDevice;
 }
@@ -60,7 +60,7 @@ int launch_value_forward(const void*, int64_t, const void*, int64_t, int64_t, bo
   return kNoDevice;
 }
 int launch_value_loss(const void*, int64_t, const void*, const float*, const float*, const uint8_t*, int64_t,
-                      int64_t, const int64_t*, bool, double*, void*, float*, void*, hipStream_t) {
+                      int64_t, const int64_t*, bool, double*, void*, float*, bool, void*, hipStream_t) {
   return kNoDevice;
 }
 

@@ -39,9 +39,10 @@ int launch_running_mean_advantage(const float* rewards, const uint8_t* mask, con
                                          double* traj_adv, int64_t* n_tokens, int32_t* status, void* ws,
                                          hipStream_t st);
 
+// store, here and below: accumulated outputs are written rather than added to.
 int launch_loss(const float* logp, const float* logp_rollout, const float* adv, const uint8_t* mask,
                        int64_t T, float eps_low, float eps_high, const int64_t* n_tokens, double* loss,
-                       float* g, uint8_t* flags, int64_t* counts, void* ws, hipStream_t st);
+                       float* g, uint8_t* flags, int64_t* counts, bool store, void* ws, hipStream_t st);
 
 // The DIS loss with its workspace in a static per-device array of
 // kLossScratchBytes (no allocation); the stream must belong to the current device.
@@ -51,17 +52,19 @@ int launch_loss_noalloc(const float* logp, const float* logp_rollout, const floa
 
 int launch_ppo_loss(const float* logp, const float* logp_old, const float* logp_behav, const float* adv,
                            const uint8_t* mask, int64_t T, float eps_low, float eps_high, const int64_t* n_tokens,
-                           double* loss, float* g, uint8_t* flags, int64_t* counts, void* ws, hipStream_t st);
+                           double* loss, float* g, uint8_t* flags, int64_t* counts, bool store, void* ws,
+                           hipStream_t st);
 
 int launch_explained_variance(const float* values, const float* ret, const uint8_t* mask, int64_t T,
-                                     double* moments, double* ev, void* ws, hipStream_t st);
+                                     double* moments, double* ev, bool store, void* ws, hipStream_t st);
 
 int launch_value_forward(const void* hidden, int64_t ld_hidden, const void* w_v, int64_t T, int64_t H,
                                 bool bf16, float* v, hipStream_t st);
 
 int launch_value_loss(const void* hidden, int64_t ld_hidden, const void* w_v, const float* v,
                              const float* ret, const uint8_t* mask, int64_t T, int64_t H, const int64_t* n_tokens,
-                             bool bf16, double* loss_v, void* dhidden_v, float* dw_v, void* ws, hipStream_t st);
+                             bool bf16, double* loss_v, void* dhidden_v, float* dw_v, bool store, void* ws,
+                             hipStream_t st);
 
 // Text of a HIP status code returned by the launchers.
 const char* device_error_string(int code);

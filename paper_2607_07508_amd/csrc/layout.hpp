@@ -11,8 +11,12 @@ constexpr int64_t kRowsPerCountBlock = 1024;  // rows per block of the compactio
 constexpr int64_t kVocabBlock = 32768;        // vocabulary rows per backward dZ block (at least)
 constexpr int64_t kVocabBlockMax = 65536;     // ... and at most
 constexpr int kLossThreads = 256;
-constexpr int kLossPerThread = 8;
+constexpr int kLossPerThread = 4;             // tokens per thread before blocks take a second turn
 constexpr int kLossMaxBlocks = 2048;
+// Threads take one quad of tokens at a time up to this many tokens (every thread then has
+// one), two beyond, for the loads in flight.
+constexpr int64_t kLossOneQuadTokens = int64_t{kLossMaxBlocks} * kLossThreads * kLossPerThread;
+static_assert(kLossPerThread == 4, "one quad");
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline int64_t ceil_div(int64_t x, int64_t m) { return (x + m - 1) / m; }
@@ -179,7 +183,7 @@ inline size_t advantage_workspace(int64_t T) {
 // sao_clipped_loss
 struct LossLayout {
   int64_t blocks;
-  size_t part_f, part_i, n_count, total;
+  size_t part_f, part_i, part_n, total;
 };
 
 inline LossLayout loss_layout(int64_t T) {
@@ -191,16 +195,16 @@ inline LossLayout loss_layout(int64_t T) {
   Carve c;
   L.part_f = c.take(16 * static_cast<size_t>(blocks));   // two doubles per block
   L.part_i = c.take(40 * static_cast<size_t>(blocks));   // five int64 per block
-  L.n_count = c.take(8);
+  L.part_n = c.take(8 * static_cast<size_t>(blocks));    // the mask count's partials
   L.total = c.off;
   return L;
 }
 
-// The largest sao_clipped_loss workspace (kLossMaxBlocks blocks; the three pieces
-// are 256-byte multiples), the size of sao_clipped_loss_noalloc's static scratch.
+// The largest sao_clipped_loss workspace (kLossMaxBlocks blocks; the pieces are
+// 256-byte multiples), the size of sao_clipped_loss_noalloc's static scratch.
 // Every T fits, since the block count is capped.
-constexpr size_t kLossScratchBytes = 16 * kLossMaxBlocks + 40 * kLossMaxBlocks + 256;
-static_assert((16 * kLossMaxBlocks) % 256 == 0 && (40 * kLossMaxBlocks) % 256 == 0, "pieces stay aligned");
+constexpr size_t kLossScratchBytes = (16 + 40 + 8) * kLossMaxBlocks;
+static_assert(8 * kLossMaxBlocks % 256 == 0, "pieces stay aligned");
 
 // sao_step_advantage: the head, then a step table of T entries (a trajectory's
 // steps sit at its own token offset): start and end (int32), and two doubles
@@ -247,7 +251,7 @@ constexpr int64_t kValueCountBlocks = 1024;   // blocks of the mask count when N
 
 struct ValueLayout {
   int64_t row_blocks, count_blocks;
-  size_t part_cnt, n_count, part_loss, part_dw, total;
+  size_t part_cnt, part_loss, part_dw, total;
 };
 
 inline ValueLayout value_layout(int64_t T, int64_t H) {
@@ -258,7 +262,6 @@ inline ValueLayout value_layout(int64_t T, int64_t H) {
   if (L.count_blocks < 1) L.count_blocks = 1;
   Carve c;
   L.part_cnt = c.take(8 * static_cast<size_t>(L.count_blocks));
-  L.n_count = c.take(8);
   L.part_loss = c.take(8 * static_cast<size_t>(L.row_blocks));
   L.part_dw = c.take(4 * static_cast<size_t>(L.row_blocks) * static_cast<size_t>(H));
   L.total = c.off;

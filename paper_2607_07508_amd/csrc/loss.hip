@@ -5,6 +5,7 @@
 // float64, g = d loss / d logp, and per-block partial sums (loss terms in float64,
 // counts in int64) reduced in a fixed order by a one-block final kernel, so
 // results do not depend on scheduling.
+#include <cmath>
 #include <mutex>
 
 #include "common.hpp"
@@ -15,12 +16,10 @@
 
 namespace sao {
 
-static_assert(64 * kLossPerThread == kWalkChunk, "one wave chunk is 64 lanes x 8 tokens");
-
 // Per-thread running sums of one call.
 struct LossAcc {
   double sL = 0.0, sS = 0.0;
-  int64_t c[5] = {0, 0, 0, 0, 0};
+  int32_t c[5] = {0, 0, 0, 0, 0};  // T fits 31 bits
 };
 
 // Whether d lies within a margin of a band edge in log space. fp64 exp is
@@ -32,15 +31,16 @@ __device__ __forceinline__ bool near_edge(double d, double edge) {
 }
 
 // The clip edges 1 - eps_low and 1 + eps_high, in ratio and in log-ratio space,
-// and comparisons of a ratio r = exp(d) with them, decided as in float64.
+// and comparisons of a ratio r = exp(d) with them, decided as in float64. Made on the
+// host: two float64 logarithms per thread otherwise.
 struct Band {
   double lo, hi, ln_lo, ln_hi;
 
-  __device__ Band(float eps_low, float eps_high) {
+  Band(float eps_low, float eps_high) {
     lo = 1.0 - static_cast<double>(eps_low);
     hi = 1.0 + static_cast<double>(eps_high);
-    ln_lo = lo > 0.0 ? log(lo) : 0.0;
-    ln_hi = log(hi);
+    ln_lo = lo > 0.0 ? std::log(lo) : 0.0;
+    ln_hi = std::log(hi);
   }
   // r <= max(lo, 0), the lower edge of the DIS band. A ratio is never negative,
   // so with eps_low >= 1 only r = 0 (log pi = -inf, or exp underflow) falls below
@@ -125,30 +125,31 @@ __device__ __forceinline__ uint8_t ppo_token(bool active, float lpf, float loldf
 
 // The block's partial sums: part_f gets sL and sS, part_i the five counts.
 __device__ __forceinline__ void store_partials(const LossAcc& acc, double* part_f, int64_t* part_i) {
-  __shared__ double shd[kLossThreads / 64];
-  __shared__ int64_t shi[kLossThreads / 64];
-  const double sL = block_sum<kLossThreads>(acc.sL, shd);
-  const double sS = block_sum<kLossThreads>(acc.sS, shd);
-  int64_t tot[5];
+  __shared__ double shd[kLossThreads / 64][2];
+  __shared__ int32_t shi[kLossThreads / 64][5];
+  double s[2] = {acc.sL, acc.sS};
+  int32_t tot[5];
 #pragma unroll
-  for (int i = 0; i < 5; ++i) tot[i] = block_sum<kLossThreads>(acc.c[i], shi);
+  for (int i = 0; i < 5; ++i) tot[i] = acc.c[i];
+  block_sums<kLossThreads>(s, shd);
+  block_sums<kLossThreads>(tot, shi);
   if (threadIdx.x == 0) {
-    part_f[2 * blockIdx.x] = sL;
-    part_f[2 * blockIdx.x + 1] = sS;
+    part_f[2 * blockIdx.x] = s[0];
+    part_f[2 * blockIdx.x + 1] = s[1];
 #pragma unroll
     for (int i = 0; i < 5; ++i) part_i[5 * blockIdx.x + i] = tot[i];
   }
 }
 
+template <int QUADS>
 __global__ __launch_bounds__(kLossThreads) void k_loss(const float* logp, const float* lro, const float* adv,
-                                                       const uint8_t* mask, int64_t T, float eps_low,
-                                                       float eps_high, const int64_t* n_ptr, double* part_f,
-                                                       int64_t* part_i, float* g, uint8_t* flags, bool vec_ok) {
-  const int64_t N = *n_ptr;
-  const Band bd(eps_low, eps_high);
+                                                       const uint8_t* mask, int64_t T, Band bd, TokenCount count,
+                                                       double* part_f, int64_t* part_i, float* g, uint8_t* flags,
+                                                       bool vec_ok) {
+  const int64_t N = count.get<kLossThreads>();
   const double invN = N > 0 ? 1.0 / static_cast<double>(N) : 0.0;
   LossAcc acc;
-  walk_tokens<kLossThreads>(
+  walk_tokens<kLossThreads, QUADS>(
       T, vec_ok,
       [&](int64_t t) {
         const f32x4_t l4 = *reinterpret_cast<const f32x4_t*>(logp + t);
@@ -175,17 +176,15 @@ __global__ __launch_bounds__(kLossThreads) void k_loss(const float* logp, const 
   store_partials(acc, part_f, part_i);
 }
 
-template <bool kWeighted>
+template <bool kWeighted, int QUADS>
 __global__ __launch_bounds__(kLossThreads) void k_ppo(const float* logp, const float* lold, const float* lb,
-                                                      const float* adv, const uint8_t* mask, int64_t T,
-                                                      float eps_low, float eps_high, const int64_t* n_ptr,
-                                                      double* part_f, int64_t* part_i, float* g, uint8_t* flags,
-                                                      bool vec_ok) {
-  const int64_t N = *n_ptr;
-  const Band bd(eps_low, eps_high);
+                                                      const float* adv, const uint8_t* mask, int64_t T, Band bd,
+                                                      TokenCount count, double* part_f, int64_t* part_i, float* g,
+                                                      uint8_t* flags, bool vec_ok) {
+  const int64_t N = count.get<kLossThreads>();
   const double invN = N > 0 ? 1.0 / static_cast<double>(N) : 0.0;
   LossAcc acc;
-  walk_tokens<kLossThreads>(
+  walk_tokens<kLossThreads, QUADS>(
       T, vec_ok,
       [&](int64_t t) {
         const f32x4_t l4 = *reinterpret_cast<const f32x4_t*>(logp + t);
@@ -216,48 +215,42 @@ __global__ __launch_bounds__(kLossThreads) void k_ppo(const float* logp, const f
 }
 
 // Sums the block partials in a fixed order; adds -sL/N (and, when n_loss == 2,
-// -sS/N) to loss and the counts to counts.
+// -sS/N) to loss and the counts to counts, or with `store` to zeros instead of what
+// they hold. N is *n_ptr, or this call's mask count (the first of the counts).
 __global__ __launch_bounds__(kLossThreads) void k_loss_final(const double* part_f, const int64_t* part_i,
-                                                             int nblk, const int64_t* n_ptr, int n_loss,
+                                                             int nblk, const int64_t* n_ptr, int n_loss, bool store,
                                                              double* loss, int64_t* counts) {
-  __shared__ double shd[kLossThreads / 64];
-  __shared__ int64_t shi[kLossThreads / 64];
-  double sL = 0.0, sS = 0.0;
+  __shared__ double shd[kLossThreads / 64][2];
+  __shared__ int64_t shi[kLossThreads / 64][5];
+  double s[2] = {0.0, 0.0};
   int64_t c[5] = {0, 0, 0, 0, 0};
   for (int i = threadIdx.x; i < nblk; i += kLossThreads) {
-    sL += part_f[2 * i];
-    sS += part_f[2 * i + 1];
+    s[0] += part_f[2 * i];
+    s[1] += part_f[2 * i + 1];
 #pragma unroll
     for (int k = 0; k < 5; ++k) c[k] += part_i[5 * i + k];
   }
-  sL = block_sum<kLossThreads>(sL, shd);
-  sS = block_sum<kLossThreads>(sS, shd);
-  int64_t tot[5];
-#pragma unroll
-  for (int k = 0; k < 5; ++k) tot[k] = block_sum<kLossThreads>(c[k], shi);
+  block_sums<kLossThreads>(s, shd);
+  block_sums<kLossThreads>(c, shi);
   if (threadIdx.x == 0) {
-    const int64_t N = *n_ptr;
-    if (N > 0) {
-      loss[0] += -sL / static_cast<double>(N);
-      if (n_loss > 1) loss[1] += -sS / static_cast<double>(N);
-    }
+    const int64_t N = n_ptr ? *n_ptr : c[0];
+    for (int k = 0; k < n_loss; ++k)
+      if (N > 0 || store) loss[k] = (store ? 0.0 : loss[k]) + (N > 0 ? -s[k] / static_cast<double>(N) : 0.0);
 #pragma unroll
-    for (int k = 0; k < 5; ++k) counts[k] += tot[k];
+    for (int k = 0; k < 5; ++k) counts[k] = (store ? 0 : counts[k]) + c[k];
   }
 }
 
 namespace {
 
-// N from the caller, or the mask count of this call computed into the workspace.
-const int64_t* token_count(const int64_t* n_tokens, const uint8_t* mask, int64_t T, const LossLayout& L,
-                           char* w8, hipStream_t st) {
-  if (n_tokens) return n_tokens;
-  int64_t* part_i = reinterpret_cast<int64_t*>(w8 + L.part_i);
-  int64_t* total = reinterpret_cast<int64_t*>(w8 + L.n_count);
-  const int nblk = static_cast<int>(L.blocks);
-  hipLaunchKernelGGL(k_mask_count<kLossThreads>, dim3(nblk), dim3(kLossThreads), 0, st, mask, T, part_i);
-  hipLaunchKernelGGL(k_count_total<kLossThreads>, dim3(1), dim3(kLossThreads), 0, st, part_i, nblk, total);
-  return total;
+// N from the caller, or the mask count of this call from partials in the workspace.
+TokenCount token_count(const int64_t* n_tokens, const uint8_t* mask, int64_t T, const LossLayout& L, char* w8,
+                       hipStream_t st) {
+  if (n_tokens) return {n_tokens, nullptr, 0};
+  int64_t* part = reinterpret_cast<int64_t*>(w8 + L.part_n);
+  const int nblk = static_cast<int>((L.blocks + 7) / 8);  // 32 mask bytes a thread
+  hipLaunchKernelGGL(k_mask_count<kLossThreads>, dim3(nblk), dim3(kLossThreads), 0, st, mask, T, part);
+  return {nullptr, part, nblk};
 }
 
 bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
@@ -266,18 +259,19 @@ bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p
 
 int launch_loss(const float* logp, const float* logp_rollout, const float* adv, const uint8_t* mask,
                        int64_t T, float eps_low, float eps_high, const int64_t* n_tokens, double* loss,
-                       float* g, uint8_t* flags, int64_t* counts, void* ws, hipStream_t st) {
+                       float* g, uint8_t* flags, int64_t* counts, bool store, void* ws, hipStream_t st) {
   const LossLayout L = loss_layout(T);
   char* w8 = static_cast<char*>(ws);
   double* part_f = reinterpret_cast<double*>(w8 + L.part_f);
   int64_t* part_i = reinterpret_cast<int64_t*>(w8 + L.part_i);
   const int nblk = static_cast<int>(L.blocks);
-  const int64_t* n_ptr = token_count(n_tokens, mask, T, L, w8, st);
+  const TokenCount count = token_count(n_tokens, mask, T, L, w8, st);
   const bool vec_ok = aligned(logp, 16) && aligned(logp_rollout, 16) && aligned(adv, 16) && aligned(g, 16) &&
                       aligned(mask, 4) && aligned(flags, 4);
-  hipLaunchKernelGGL(k_loss, dim3(nblk), dim3(kLossThreads), 0, st, logp, logp_rollout, adv, mask, T,
-                     eps_low, eps_high, n_ptr, part_f, part_i, g, flags, vec_ok);
-  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossThreads), 0, st, part_f, part_i, nblk, n_ptr, 2, loss,
+  const auto kernel = T <= kLossOneQuadTokens ? k_loss<1> : k_loss<2>;
+  hipLaunchKernelGGL(kernel, dim3(nblk), dim3(kLossThreads), 0, st, logp, logp_rollout, adv, mask, T,
+                     Band(eps_low, eps_high), count, part_f, part_i, g, flags, vec_ok);
+  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossThreads), 0, st, part_f, part_i, nblk, n_tokens, 2, store, loss,
                      counts);
   return hipGetLastError();
 }
@@ -329,28 +323,27 @@ int launch_loss_noalloc(const float* logp, const float* logp_rollout, const floa
   if (loss_layout(T).total > kLossScratchBytes) return hipErrorInvalidValue;  // the caller checked this
   // Every piece of the layout is written before it is read (block partials, then
   // the mask count when n_tokens is NULL), so nothing needs clearing between calls.
-  return launch_loss(logp, logp_rollout, adv, mask, T, eps_low, eps_high, n_tokens, loss, g, flags, counts,
+  return launch_loss(logp, logp_rollout, adv, mask, T, eps_low, eps_high, n_tokens, loss, g, flags, counts, false,
                      slot.ptr, st);
 }
 
 int launch_ppo_loss(const float* logp, const float* logp_old, const float* logp_behav, const float* adv,
                            const uint8_t* mask, int64_t T, float eps_low, float eps_high, const int64_t* n_tokens,
-                           double* loss, float* g, uint8_t* flags, int64_t* counts, void* ws, hipStream_t st) {
+                           double* loss, float* g, uint8_t* flags, int64_t* counts, bool store, void* ws,
+                           hipStream_t st) {
   const LossLayout L = loss_layout(T);
   char* w8 = static_cast<char*>(ws);
   double* part_f = reinterpret_cast<double*>(w8 + L.part_f);
   int64_t* part_i = reinterpret_cast<int64_t*>(w8 + L.part_i);
   const int nblk = static_cast<int>(L.blocks);
-  const int64_t* n_ptr = token_count(n_tokens, mask, T, L, w8, st);
+  const TokenCount count = token_count(n_tokens, mask, T, L, w8, st);
   const bool vec_ok = aligned(logp, 16) && aligned(logp_old, 16) && aligned(logp_behav, 16) && aligned(adv, 16) &&
                       aligned(g, 16) && aligned(mask, 4) && aligned(flags, 4);
-  if (logp_behav)
-    hipLaunchKernelGGL(k_ppo<true>, dim3(nblk), dim3(kLossThreads), 0, st, logp, logp_old, logp_behav, adv, mask,
-                       T, eps_low, eps_high, n_ptr, part_f, part_i, g, flags, vec_ok);
-  else
-    hipLaunchKernelGGL(k_ppo<false>, dim3(nblk), dim3(kLossThreads), 0, st, logp, logp_old, logp_behav, adv, mask,
-                       T, eps_low, eps_high, n_ptr, part_f, part_i, g, flags, vec_ok);
-  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossThreads), 0, st, part_f, part_i, nblk, n_ptr, 1, loss,
+  const bool one = T <= kLossOneQuadTokens;
+  const auto kernel = logp_behav ? (one ? k_ppo<true, 1> : k_ppo<true, 2>) : (one ? k_ppo<false, 1> : k_ppo<false, 2>);
+  hipLaunchKernelGGL(kernel, dim3(nblk), dim3(kLossThreads), 0, st, logp, logp_old, logp_behav, adv, mask, T,
+                     Band(eps_low, eps_high), count, part_f, part_i, g, flags, vec_ok);
+  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossThreads), 0, st, part_f, part_i, nblk, n_tokens, 1, store, loss,
                      counts);
   return hipGetLastError();
 }

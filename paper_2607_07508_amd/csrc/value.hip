@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kValueThreads) void k_value_forward(const typename 
 template <class E>
 __global__ __launch_bounds__(kValueThreads) void k_value_rows(
     const typename E::storage* hidden, int64_t ld, const typename E::storage* w, const float* v,
-    const float* ret, const uint8_t* mask, int64_t T, int64_t H, const int64_t* n_ptr,
+    const float* ret, const uint8_t* mask, int64_t T, int64_t H, TokenCount count,
     typename E::storage* dhidden, double* part_loss, float* part_dw) {
   constexpr int P = E::kPerChunk;
   __shared__ float s_dv[kValueRows];
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kValueThreads) void k_value_rows(
   const int tid = threadIdx.x;
   const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kValueRows;
   const int nrows = static_cast<int>(T - r0 < kValueRows ? T - r0 : kValueRows);
-  const int64_t N = *n_ptr;
+  const int64_t N = count.get<kValueThreads>();
   const double invN = N > 0 ? 1.0 / static_cast<double>(N) : 0.0;
   double l = 0.0;
   if (tid < kValueRows) {
@@ -129,14 +129,14 @@ __global__ __launch_bounds__(kValueThreads) void k_value_rows(
   for (int e = 0; e < P; ++e) out[e] = acc[e];
 }
 
-// dw_v[col] += sum over row blocks; block 0 also adds the loss. A block takes
+// dw_v[col] += sum over row blocks; block 0 also adds the loss (with `store`, to zeros). A block takes
 // 64 columns: wave w sums row blocks w, w + 4, w + 8, ... into 8 partial sums
 // per lane (so that 8 loads are in flight), which it combines in a fixed order;
 // then the 4 waves' sums are added in wave order. Every run adds in the same
 // order, so the result is deterministic.
 __global__ __launch_bounds__(kValueThreads) void k_value_final(const float* part_dw, const double* part_loss,
                                                                int64_t row_blocks, int64_t H,
-                                                               const int64_t* n_ptr, double* loss_v,
+                                                               TokenCount count, bool store, double* loss_v,
                                                                float* dw_v) {
   constexpr int kWaves = kValueThreads / 64;
   constexpr int kLanes = 8;
@@ -147,8 +147,9 @@ __global__ __launch_bounds__(kValueThreads) void k_value_final(const float* part
     double l = 0.0;
     for (int64_t i = threadIdx.x; i < row_blocks; i += kValueThreads) l += part_loss[i];
     l = block_sum<kValueThreads>(l, s_red);
-    const int64_t N = *n_ptr;
-    if (threadIdx.x == 0 && N > 0) loss_v[0] += l / static_cast<double>(N);
+    const int64_t N = count.get<kValueThreads>();
+    if (threadIdx.x == 0 && (N > 0 || store))
+      loss_v[0] = (store ? 0.0 : loss_v[0]) + (N > 0 ? l / static_cast<double>(N) : 0.0);
   }
   const int64_t col = static_cast<int64_t>(blockIdx.x) * 64 + lane;
   float acc[kLanes];
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(kValueThreads) void k_value_final(const float* part
     float t = s_col[0][lane];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) t += s_col[w][lane];
-    dw_v[col] += t;
+    dw_v[col] = (store ? 0.0f : dw_v[col]) + t;
   }
 }
 
@@ -189,17 +190,16 @@ int launch_value_forward(const void* hidden, int64_t ld_hidden, const void* w_v,
 
 int launch_value_loss(const void* hidden, int64_t ld_hidden, const void* w_v, const float* v,
                              const float* ret, const uint8_t* mask, int64_t T, int64_t H, const int64_t* n_tokens,
-                             bool bf16, double* loss_v, void* dhidden_v, float* dw_v, void* ws, hipStream_t st) {
+                             bool bf16, double* loss_v, void* dhidden_v, float* dw_v, bool store, void* ws,
+                             hipStream_t st) {
   const ValueLayout L = value_layout(T, H);
   char* w8 = static_cast<char*>(ws);
-  const int64_t* n_ptr = n_tokens;
-  if (!n_ptr) {
+  TokenCount count{n_tokens, nullptr, 0};
+  if (!n_tokens) {
     int64_t* part = reinterpret_cast<int64_t*>(w8 + L.part_cnt);
-    int64_t* total = reinterpret_cast<int64_t*>(w8 + L.n_count);
     const int nblk = static_cast<int>(L.count_blocks);
     hipLaunchKernelGGL(k_mask_count<kValueThreads>, dim3(nblk), dim3(kValueThreads), 0, st, mask, T, part);
-    hipLaunchKernelGGL(k_count_total<kValueThreads>, dim3(1), dim3(kValueThreads), 0, st, part, nblk, total);
-    n_ptr = total;
+    count = {nullptr, part, nblk};
   }
   double* part_loss = reinterpret_cast<double*>(w8 + L.part_loss);
   float* part_dw = reinterpret_cast<float*>(w8 + L.part_dw);
@@ -207,14 +207,14 @@ int launch_value_loss(const void* hidden, int64_t ld_hidden, const void* w_v, co
   const dim3 grid(static_cast<unsigned>(L.row_blocks), static_cast<unsigned>(ceil_div(H / P, kValueThreads)));
   if (bf16)
     hipLaunchKernelGGL(k_value_rows<BF16>, grid, dim3(kValueThreads), 0, st, static_cast<const uint16_t*>(hidden),
-                       ld_hidden, static_cast<const uint16_t*>(w_v), v, ret, mask, T, H, n_ptr,
+                       ld_hidden, static_cast<const uint16_t*>(w_v), v, ret, mask, T, H, count,
                        static_cast<uint16_t*>(dhidden_v), part_loss, part_dw);
   else
     hipLaunchKernelGGL(k_value_rows<F32>, grid, dim3(kValueThreads), 0, st, static_cast<const float*>(hidden),
-                       ld_hidden, static_cast<const float*>(w_v), v, ret, mask, T, H, n_ptr,
+                       ld_hidden, static_cast<const float*>(w_v), v, ret, mask, T, H, count,
                        static_cast<float*>(dhidden_v), part_loss, part_dw);
   hipLaunchKernelGGL(k_value_final, dim3(static_cast<unsigned>(ceil_div(H, 64))), dim3(kValueThreads), 0,
-                     st, part_dw, part_loss, L.row_blocks, H, n_ptr, loss_v, dw_v);
+                     st, part_dw, part_loss, L.row_blocks, H, count, store, loss_v, dw_v);
   return hipGetLastError();
 }
 
