@@ -94,6 +94,40 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _Plain:
+    """Stands in for _fast while libsao.so is not built: every call is left to Python."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+_fast_module = None
+
+
+def _fast():
+    """The native argument marshalling (csrc/fast.cpp), bound to the loaded library. Its functions
+    return None for calls that are not plain, which the code below then takes."""
+    global _fast_module
+    if _fast_module is None:
+        if not os.path.exists(LIB_PATH):
+            return _Plain()
+        from . import _fast as module
+        L = lib()
+        names = ("sao_workspace_size", "sao_advantage", "sao_step_advantage", "sao_group_advantage",
+                 "sao_clipped_loss_store", "sao_ppo_loss_store", "sao_explained_variance_store")
+        module.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names},
+                    torch._C._cuda_getCurrentRawStream)
+        _fast_module = module
+    return _fast_module
+
+
+def _done(out):
+    """The outputs of a _fast call, or the error its status stands for."""
+    if type(out) is int:
+        _check(out)
+    return out
+
+
 def _check(code: int) -> None:
     if code != 0:
         raise SaoError(code, lib().sao_last_error_message().decode())
@@ -191,6 +225,9 @@ def advantage(values: torch.Tensor, rewards: torch.Tensor, mask: torch.Tensor, c
               gamma: float = 1.0, lam: float = 1.0, alpha: float = 0.0,
               status: Optional[torch.Tensor] = None, want_count: bool = True):
     """Skip-observation GAE: (adv, ret, n_tokens) with n_tokens a device int64 scalar."""
+    out = _fast().advantage(values, rewards, mask, cu_seqlens, gamma, lam, alpha, status, want_count)
+    if out is not None:
+        return _done(out)
     T = values.shape[0]
     B = cu_seqlens.shape[0] - 1
     dev = values.device
@@ -215,12 +252,15 @@ def step_advantage(values: torch.Tensor, rewards: torch.Tensor, mask: torch.Tens
                    gamma: float = 1.0, lam: float = 1.0, alpha: float = 0.0, step_value: str = "average",
                    status: Optional[torch.Tensor] = None, want_last: bool = True, want_count: bool = True):
     """Step-level GAE: (adv, ret, last or None, n_tokens or None); step_value "average" or "last"."""
-    T = values.shape[0]
-    B = cu_seqlens.shape[0] - 1
-    dev = values.device
     form = {"average": STEP_AVERAGE, "last": STEP_LAST}.get(step_value)
     if form is None:
         raise ValueError(f"step_value must be 'average' or 'last', not {step_value!r}")
+    out = _fast().step_advantage(values, rewards, mask, cu_seqlens, gamma, lam, alpha, form, status, want_last, want_count)
+    if out is not None:
+        return _done(out)
+    T = values.shape[0]
+    B = cu_seqlens.shape[0] - 1
+    dev = values.device
     _vec(values, "values", torch.float32, T, dev)
     _vec(rewards, "rewards", torch.float32, T, dev)
     _vec(mask, "mask", torch.uint8, T, dev)
@@ -253,6 +293,9 @@ def _segment_inputs(rewards, mask, cu_seqlens, status):
 def group_advantage(rewards: torch.Tensor, mask: torch.Tensor, cu_seqlens: torch.Tensor, group_size: int,
                     eps_stab: float, status: Optional[torch.Tensor] = None, want_count: bool = True):
     """GRPO advantage: (adv [T] f32, traj_adv [B] f64, traj_reward [B] f64, n_tokens or None)."""
+    out = _fast().group_advantage(rewards, mask, cu_seqlens, group_size, eps_stab, status, want_count)
+    if out is not None:
+        return _done(out)
     T, B, dev = _segment_inputs(rewards, mask, cu_seqlens, status)
     adv = torch.empty(T, dtype=torch.float32, device=dev)
     traj_reward = torch.empty(B, dtype=torch.float64, device=dev)
@@ -302,6 +345,11 @@ def clipped_loss(logp: torch.Tensor, logp_rollout: torch.Tensor, adv: torch.Tens
                  eps_low: float, eps_high: float, n_tokens: Optional[torch.Tensor] = None,
                  loss: Optional[torch.Tensor] = None, counts: Optional[torch.Tensor] = None):
     """DIS loss: (loss[2] f64 +=, g, flags, counts[5] i64 +=). Accumulators start from zero if not given."""
+    store = loss is None and counts is None  # both start with this call
+    if store:
+        out = _fast().clipped_loss(logp, logp_rollout, adv, mask, eps_low, eps_high, n_tokens)
+        if out is not None:
+            return _done(out)
     T = logp.shape[0]
     dev = logp.device
     _vec(logp, "logp", torch.float32, T, dev)
@@ -309,7 +357,6 @@ def clipped_loss(logp: torch.Tensor, logp_rollout: torch.Tensor, adv: torch.Tens
     _vec(adv, "adv", torch.float32, T, dev)
     _vec(mask, "mask", torch.uint8, T, dev)
     _vec(n_tokens, "n_tokens", torch.int64, 1, dev, optional=True)
-    store = loss is None and counts is None  # both start with this call
     if store:
         loss, counts = _fresh(T, 2, torch.float64, dev), _fresh(T, 5, torch.int64, dev)
     elif loss is None:
@@ -362,6 +409,11 @@ def ppo_loss(logp: torch.Tensor, logp_old: torch.Tensor, adv: torch.Tensor, mask
              counts: Optional[torch.Tensor] = None):
     """Clipped surrogate (standard, clip-higher, or decoupled with logp_behav):
     (loss[1] f64 +=, g, flags, counts[5] i64 +=). Accumulators start from zero if not given."""
+    store = loss is None and counts is None  # both start with this call
+    if store:
+        out = _fast().ppo_loss(logp, logp_old, logp_behav, adv, mask, eps_low, eps_high, n_tokens)
+        if out is not None:
+            return _done(out)
     T = logp.shape[0]
     dev = logp.device
     _vec(logp, "logp", torch.float32, T, dev)
@@ -370,7 +422,6 @@ def ppo_loss(logp: torch.Tensor, logp_old: torch.Tensor, adv: torch.Tensor, mask
     _vec(adv, "adv", torch.float32, T, dev)
     _vec(mask, "mask", torch.uint8, T, dev)
     _vec(n_tokens, "n_tokens", torch.int64, 1, dev, optional=True)
-    store = loss is None and counts is None  # both start with this call
     if store:
         loss, counts = _fresh(T, 1, torch.float64, dev), _fresh(T, 5, torch.int64, dev)
     elif loss is None:
@@ -394,12 +445,16 @@ def explained_variance(values: torch.Tensor, ret: torch.Tensor, mask: torch.Tens
                        moments: Optional[torch.Tensor] = None):
     """(ev [1] f64, moments [5] f64): EV = 1 - Var(R - V) / Var(R) over mask tokens, with this
     call's tokens combined into `moments` (which start from zero if not given) so chunked calls cover a batch."""
+    store = moments is None
+    if store:
+        out = _fast().explained_variance(values, ret, mask)
+        if out is not None:
+            return _done(out)
     T = values.shape[0]
     dev = values.device
     _vec(values, "values", torch.float32, T, dev)
     _vec(ret, "ret", torch.float32, T, dev)
     _vec(mask, "mask", torch.uint8, T, dev)
-    store = moments is None
     if store:
         moments = _fresh(T, 5, torch.float64, dev)
     _vec(moments, "moments", torch.float64, 5, dev)

@@ -15,6 +15,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsao.so")
+FAST_MODULE = os.path.join(PKG, "_fast.so")        # argument marshalling of the per-token passes
 PROBE_LIB = os.path.join(PKG, "libsao_probe.so")   # bench.py --mfma-ceiling only
 ARCH = os.environ.get("SAO_OFFLOAD_ARCH", "gfx950")
 
@@ -46,10 +47,33 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
+def _build_fast() -> None:
+    import sysconfig
+
+    import torch
+    gxx = shutil.which("g++")
+    if gxx is None:
+        raise RuntimeError("g++ not found")
+    root = os.path.dirname(torch.__file__)
+    tmp = FAST_MODULE + ".tmp"
+    cmd = [gxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "fast.cpp"), "-o", tmp,
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"compile failed: fast.cpp\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, FAST_MODULE)
+
+
 def build(extra=(), verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        fast = ex.submit(_build_fast)
         objs = list(ex.map(lambda s: _compile(s, list(extra)), SOURCES))
+        fast.result()
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -65,7 +89,7 @@ def build(extra=(), verbose: bool = False) -> str:
         raise RuntimeError(f"link failed\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     os.replace(ptmp, PROBE_LIB)
     if verbose:
-        print(f"built {LIB} and {PROBE_LIB}")
+        print(f"built {LIB}, {FAST_MODULE} and {PROBE_LIB}")
     return LIB
 
 
