@@ -672,7 +672,7 @@ int launch_advantage(const float* values, const float* rewards, const uint8_t* m
     return hipGetLastError();
   }
   hipLaunchKernelGGL((k_check_segments<256, kCountSlots>), dim3(1), dim3(256), 0, st, cu_seqlens, B, T, bad, slots,
-                     status);
+                     status, nullptr);
   hipLaunchKernelGGL(k_advantage, dim3(B), dim3(kScanThreads), 0, st, values, rewards, mask, cu_seqlens,
                      B, T, gamma, lam, alpha, adv, ret, slots, bad, vec_ok);
   if (n_tokens) hipLaunchKernelGGL(k_slots_total<kCountSlots>, dim3(1), dim3(64), 0, st, slots, n_tokens);

@@ -17,11 +17,13 @@ __device__ __forceinline__ bool segments_bad(const int32_t* cu, int32_t B, int64
 }
 
 // One block: cu_seqlens must rise from 0 to T without decreasing. Sets *bad (0/1),
-// zeroes the kSlots count slots, and flags the status word.
+// zeroes the kSlots count slots (and *n_tokens, if given), and flags the status word.
 template <int THREADS, int kSlots>
 __global__ __launch_bounds__(THREADS) void k_check_segments(const int32_t* cu, int32_t B, int64_t T, int32_t* bad,
-                                                            int64_t* slots, int32_t* status) {
+                                                            int64_t* slots, int32_t* status,
+                                                            int64_t* n_tokens = nullptr) {
   for (int i = threadIdx.x; i < kSlots; i += THREADS) slots[i] = 0;
+  if (n_tokens && threadIdx.x == 0) *n_tokens = 0;
   const bool b = segments_bad<THREADS>(cu, B, T);
   if (threadIdx.x == 0) {
     *bad = b ? 1 : 0;
@@ -29,11 +31,11 @@ __global__ __launch_bounds__(THREADS) void k_check_segments(const int32_t* cu, i
   }
 }
 
-// Adds a workgroup's loss-mask count to its slot. Many workgroups adding to one
+// Adds a workgroup's loss-mask count to its slot (none when slots is null). Many workgroups adding to one
 // address serialise at the cache; spread over the slots they do not.
 template <int kSlots>
 __device__ __forceinline__ void add_count(int64_t* slots, int64_t cnt) {
-  if (cnt) atomicAdd(reinterpret_cast<unsigned long long*>(slots + blockIdx.x % kSlots), static_cast<unsigned long long>(cnt));
+  if (cnt && slots) atomicAdd(reinterpret_cast<unsigned long long*>(slots + blockIdx.x % kSlots), static_cast<unsigned long long>(cnt));
 }
 
 // *n_tokens = the sum of the kSlots slots (one wave).

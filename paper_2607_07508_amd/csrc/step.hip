@@ -7,14 +7,14 @@
 //   A_i = R_i + gamma V_{i+1} - V_i + gamma lambda_b A_{i+1},  G_i = R_i + gamma G_{i+1}
 // with V_n = A_n = G_n = 0 and lambda_b = 1 - 1/(alpha n) when alpha > 0.
 //
-// One workgroup per trajectory, three phases separated by barriers:
-//  1. left to right over 2048-token tiles: each token's step starts a new
+// One workgroup of THREADS threads per trajectory, three phases separated by barriers:
+//  1. left to right over tiles of 8 THREADS tokens: each token's step starts a new
 //     segment (a step's run and the observations after it); a block scan numbers
 //     the steps and a segmented block scan sums values (on the run) and rewards
 //     (over the segment), with the open segment's sums carried from tile to tile.
 //     Each step's start, end and sums (or last value) go to a per-trajectory
 //     table in the workspace, written once, by the thread holding the token;
-//  2. the recurrence over steps: each thread takes a contiguous chunk of steps,
+//  2. the recurrence over steps: each of 256 threads takes a contiguous chunk of steps,
 //     summarises it as an affine map of the state entering from its right, one
 //     thread chains the chunk maps, and each thread replays its chunk;
 //  3. each wave writes its steps' tokens: A_i and G_i on the run, zeros on the
@@ -27,9 +27,8 @@
 
 namespace sao {
 
-constexpr int kStepThreads = 256;
-constexpr int kStepPer = 8;                               // tokens per thread per tile
-constexpr int kStepTile = kStepThreads * kStepPer;
+constexpr int kStepPer = 8;     // tokens per thread per tile
+constexpr int kStepChunks = 256;  // chunks of steps in phase 2
 
 namespace {
 // Lane moves by DPP (CTRL, ROW_MASK): VALU operations, no LDS crossbar. Lanes
@@ -70,6 +69,7 @@ __device__ __forceinline__ Seg dpp_seg(const Seg& x) {
 // starts before it in this call. `out` gets everything (carry's sums included,
 // n = the call's starts) for the next call. Successive calls alternate between
 // the two halves of `sh`, so no call waits for the previous one's readers.
+template <int THREADS>
 __device__ __forceinline__ Seg block_segmented_scan(const Seg& x, const Seg& carry, Seg* sh, Seg* out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   Seg incl = x;  // the empty sums on the left change nothing
@@ -85,24 +85,32 @@ __device__ __forceinline__ Seg block_segmented_scan(const Seg& x, const Seg& car
   Seg before{0, carry.v, carry.r};
   for (int w = 0; w < wave; ++w) before = seg_combine(before, sh[w]);
   Seg all = before;
-  for (int w = wave; w < kStepThreads / 64; ++w) all = seg_combine(all, sh[w]);
+  for (int w = wave; w < THREADS / 64; ++w) all = seg_combine(all, sh[w]);
   *out = all;
   return seg_combine(before, excl);
 }
 
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_step_advantage(
+// Fewer trajectories than CUs: 1024 threads each, so that the longest one, which the pass
+// waits for, takes a quarter of the tiles, and their counts are added to one address,
+// n_tokens, which the check of the segments has zeroed (64 trajectories of
+// 4096 tokens: 33 -> 24 us with the check and the count).
+constexpr int32_t kStepWideMaxB = 256;
+
+template <int THREADS, int kSlots>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_step_advantage(
     const float* values, const float* rewards, const uint8_t* mask, const int32_t* cu, int32_t B, int64_t T,
     double gamma, double lam, double alpha, bool last_value, float* adv, float* ret, uint8_t* last,
     int64_t* slots, const int32_t* bad, int32_t* tab_a, int32_t* tab_z, double* tab_v, double* tab_r,
     bool vec_ok, bool out_vec) {
-  __shared__ Seg s_seg[2][kStepThreads / 64];  // alternate tiles use alternate halves
-  __shared__ double s_map[kStepThreads][4];   // per chunk: A = cA + mA A_in, G = cG + mG G_in
-  __shared__ double s_in[kStepThreads][2];    // (A, G) entering each chunk from the right
-  __shared__ int64_t s_cnt[kStepThreads / 64];
+  constexpr int kStepTile = THREADS * kStepPer;
+  __shared__ Seg s_seg[2][THREADS / 64];  // alternate tiles use alternate halves
+  __shared__ double s_map[kStepChunks][4];   // per chunk: A = cA + mA A_in, G = cG + mG G_in
+  __shared__ double s_in[kStepChunks][2];    // (A, G) entering each chunk from the right
+  __shared__ int64_t s_cnt[THREADS / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = blockIdx.x;
   if (*bad) {
-    malformed_slice<kStepThreads, kCountSlots>(mask, B, T, adv, ret, last, slots);
+    malformed_slice<THREADS, kSlots>(mask, B, T, adv, ret, last, slots);
     return;
   }
   const int64_t s = cu[b], e = cu[b + 1];
@@ -166,7 +174,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(4)
     }
     x.n = ns;
     Seg next_carry;
-    Seg run = block_segmented_scan(x, carry, s_seg[tile & 1], &next_carry);
+    Seg run = block_segmented_scan<THREADS>(x, carry, s_seg[tile & 1], &next_carry);
     const int first = n + run.n, tot_s = next_carry.n;
     // Replay: `key` is the step whose segment holds the token (-1 before the first).
     int key = first - 1;
@@ -206,13 +214,13 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(4)
     if (lam_b < 0.0) lam_b = 0.0;
   }
   const double kappa = gamma * lam_b;
-  const int per = (n + kStepThreads - 1) / kStepThreads;
-  const int p = min(n, tid * per), q = min(n, p + per);
+  const int per = (n + kStepChunks - 1) / kStepChunks;
+  const int p = min(n, tid * per), q = min(n, p + per);  // empty from thread kStepChunks on
   auto step_value = [&](int i) {
     return last_value ? tv[i] : tv[i] / static_cast<double>(tz[i] - ta[i]);
   };
   const double v_right = q < n ? step_value(q) : 0.0;   // read before any thread overwrites the table
-  {
+  if (tid < kStepChunks) {
     double cA = 0.0, mA = 1.0, cG = 0.0, mG = 1.0, vn = v_right;
     for (int i = q - 1; i >= p; --i) {
       const double vi = step_value(i), ri = tr[i];
@@ -255,12 +263,12 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(4)
   // Phase 3: outputs. Tokens before the first step, and every token of a
   // trajectory without steps, are zero; each wave then writes its steps' spans.
   const int64_t head = n > 0 ? ta[0] : L;
-  for (int64_t t = tid; t < head; t += kStepThreads) {
+  for (int64_t t = tid; t < head; t += THREADS) {
     adv[s + t] = 0.0f;
     ret[s + t] = 0.0f;
     if (last) last[s + t] = 0;
   }
-  for (int i = wave; i < n; i += kStepThreads / 64) {
+  for (int i = wave; i < n; i += THREADS / 64) {
     const int64_t a = s + ta[i], z = s + tz[i], nxt = s + (i + 1 < n ? ta[i + 1] : L);  // global indices
     const float A = static_cast<float>(tv[i]), G = static_cast<float>(tr[i]);
     auto one = [&](int64_t t) {
@@ -292,8 +300,8 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(4)
   __syncthreads();
   if (tid == 0) {
     int64_t tot = 0;
-    for (int w = 0; w < kStepThreads / 64; ++w) tot += s_cnt[w];
-    add_count<kCountSlots>(slots, tot);
+    for (int w = 0; w < THREADS / 64; ++w) tot += s_cnt[w];
+    add_count<kSlots>(slots, tot);
   }
 }
 
@@ -306,20 +314,23 @@ int launch_step_advantage(const float* values, const float* rewards, const uint8
   const SegHead H = seg_head();
   int32_t* bad = reinterpret_cast<int32_t*>(w8 + H.bad);
   int64_t* slots = reinterpret_cast<int64_t*>(w8 + H.slots);
+  const bool wide = B <= kStepWideMaxB;
   hipLaunchKernelGGL((k_check_segments<256, kCountSlots>), dim3(1), dim3(256), 0, st, cu_seqlens, B, T, bad, slots,
-                     status);
+                     status, wide ? n_tokens : nullptr);
   // Whole in-trajectory blocks of 8 tokens use vector loads when the bases allow them.
   const bool vec_ok = ((reinterpret_cast<uintptr_t>(values) | reinterpret_cast<uintptr_t>(rewards)) & 15u) == 0 &&
                       (reinterpret_cast<uintptr_t>(mask) & 7u) == 0;
   // The output spans use 16-byte stores when adv and ret are 16-byte aligned and `last` (if given) 4-byte aligned.
   const bool out_vec = ((reinterpret_cast<uintptr_t>(adv) | reinterpret_cast<uintptr_t>(ret)) & 15u) == 0 &&
                        (reinterpret_cast<uintptr_t>(last) & 3u) == 0;
-  hipLaunchKernelGGL(k_step_advantage, dim3(B), dim3(kStepThreads), 0, st, values, rewards, mask, cu_seqlens, B, T,
-                     gamma, lam, alpha, last_value, adv, ret, last, slots, bad,
+  const auto kernel = wide ? k_step_advantage<1024, 1> : k_step_advantage<256, kCountSlots>;
+  hipLaunchKernelGGL(kernel, dim3(B), dim3(wide ? 1024 : 256), 0, st, values, rewards, mask, cu_seqlens, B, T, gamma, lam,
+                     alpha, last_value, adv, ret, last, wide ? n_tokens : slots, bad,
                      reinterpret_cast<int32_t*>(w8 + Ly.tab_a), reinterpret_cast<int32_t*>(w8 + Ly.tab_z),
                      reinterpret_cast<double*>(w8 + Ly.tab_v), reinterpret_cast<double*>(w8 + Ly.tab_r), vec_ok,
                      out_vec);
-  if (n_tokens) hipLaunchKernelGGL(k_slots_total<kCountSlots>, dim3(1), dim3(64), 0, st, slots, n_tokens);
+  if (n_tokens && !wide)
+    hipLaunchKernelGGL(k_slots_total<kCountSlots>, dim3(1), dim3(64), 0, st, slots, n_tokens);
   return hipGetLastError();
 }
 
