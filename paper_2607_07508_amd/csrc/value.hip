@@ -59,6 +59,10 @@ __global__ __launch_bounds__(kValueThreads) void k_value_forward(const typename 
   if (lane == 0) v[t] = acc;
 }
 
+// dH_v is written with non-temporal stores: they leave the memory-side cache to the
+// hidden states, which the value forward reads before and after (32,768 rows of 6144
+// over four sets of inputs in turn: the critic's calls 245 -> 215 us; with the cache
+// full of another kernel's dirty lines 257 -> 264).
 // Block (row block rb, chunk block cb): dv for kValueRows rows, dH_v for those
 // rows over 256 chunks of H, the partial dw_v of those rows, and (cb == 0) the
 // row block's float64 loss partial.
@@ -115,7 +119,7 @@ __global__ __launch_bounds__(kValueThreads) void k_value_rows(
       float o[P];
 #pragma unroll
       for (int e = 0; e < P; ++e) o[e] = d == 0.0f ? 0.0f : d * wf[e];
-      reinterpret_cast<v4u*>(dhidden + (r0 + i0 + u) * H)[c] = narrow(o, E{});
+      __builtin_nontemporal_store(narrow(o, E{}), &reinterpret_cast<v4u*>(dhidden + (r0 + i0 + u) * H)[c]);
       if (d != 0.0f) {
         float h[P];
         widen(hr[u], h, E{});
