@@ -385,8 +385,10 @@ __global__ __launch_bounds__(256) void k_fill_i64(int64_t* p, int64_t n, int64_t
 // describes a partial last vocabulary tile (st.m > 0), that tile's token tiles
 // t with t % 8 == b % 8, with the masked epilogue. Only valid token tiles (below
 // the device count) are enumerated, so no workgroup is dispatched for nothing,
-// and a workgroup takes its next tile as soon as it is free, whichever shader
-// engine it sits on. The timeline hook records tile (v, t) in slot
+// and a workgroup claims its next tile when it starts one, whichever shader engine
+// it sits on, and copies that tile's first slabs during its epilogue (log-probs of 293
+// tokens 235.7 -> 231.4 us, two 8192-token backward chunks 12.90 -> 12.79 ms against
+// claiming and copying after it). The timeline hook records tile (v, t) in slot
 // v x n_tiles + t (the partial tile as v = s.m_tiles).
 template <class E>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
