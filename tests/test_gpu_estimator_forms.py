@@ -62,3 +62,22 @@ def test_group_forms(B, G):
     assert adv.isnan().all() and traj.isnan().all() and rew.isnan().all() and int(n) == int(m.sum())
     assert int(status) == 2
     assert sao.group_advantage(_t(r), _t(m), _t(cu), G, 1e-6, want_count=False)[3] is None
+
+
+@pytest.mark.parametrize("B,T", [(3, 2000), (16, 9000), (1024, 9000), (1025, 9000), (3000, 9000)])
+def test_scan_finds_its_segments(B, T):
+    """The flat scan's search for a tile's trajectories, with few and with many of them and
+    empty ones among them; then with malformed segments."""
+    say(f"scan segments: B={B} T={T}")
+    v, r, m, cu = _batch(B, T, B)
+    adv, ret, n = sao.advantage(_t(v), _t(r), _t(m), _t(cu), 0.99, 0.9, 1.5)
+    ra, rr, rn = oracle.advantage(v, r, m, cu, 0.99, 0.9, 1.5)
+    assert int(n) == rn
+    for x, y in ((adv, ra), (ret, rr)):
+        assert (np.abs(x.cpu().numpy() - y) <= TOL_ADV * np.maximum(1.0, np.abs(y))).all()
+    for i, x in ((1, T + 9), (B // 2, -5), (0, 3)):
+        bad = cu.copy()
+        bad[i] = x
+        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        adv, ret, n = sao.advantage(_t(v), _t(r), _t(m), _t(bad), status=status)
+        assert adv.isnan().all() and ret.isnan().all() and int(n) == rn and int(status) == 2
