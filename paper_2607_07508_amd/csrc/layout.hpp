@@ -206,6 +206,18 @@ inline LossLayout loss_layout(int64_t T) {
 constexpr size_t kLossScratchBytes = (16 + 40 + 8) * kLossMaxBlocks;
 static_assert(8 * kLossMaxBlocks % 256 == 0, "pieces stay aligned");
 
+// The recurrence over a trajectory's n steps runs over kStepChunks chunks of equal length;
+// chunk i is [step_chunk_begin(n, i), step_chunk_begin(n, i + 1)), empty from kStepChunks on.
+// In 64 bits: with 1024 threads i x length passes 2^31 from 537 million steps.
+constexpr int kStepChunks = 256;
+constexpr int step_chunk_len(int n) {
+  return static_cast<int>((static_cast<int64_t>(n) + kStepChunks - 1) / kStepChunks);
+}
+constexpr int step_chunk_begin(int n, int i) {
+  const int64_t p = static_cast<int64_t>(i) * step_chunk_len(n);
+  return p < n ? static_cast<int>(p) : n;
+}
+
 // sao_step_advantage: the head, then a step table of T entries (a trajectory's
 // steps sit at its own token offset): start and end (int32), and two doubles
 // (the step's value and reward, later its advantage and return).

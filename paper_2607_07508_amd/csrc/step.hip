@@ -28,7 +28,6 @@
 namespace sao {
 
 constexpr int kStepPer = 8;     // tokens per thread per tile
-constexpr int kStepChunks = 256;  // chunks of steps in phase 2
 
 namespace {
 // Lane moves by DPP (CTRL, ROW_MASK): VALU operations, no LDS crossbar. Lanes
@@ -214,8 +213,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) vo
     if (lam_b < 0.0) lam_b = 0.0;
   }
   const double kappa = gamma * lam_b;
-  const int per = (n + kStepChunks - 1) / kStepChunks;
-  const int p = min(n, tid * per), q = min(n, p + per);  // empty from thread kStepChunks on
+  const int per = step_chunk_len(n);
+  const int p = step_chunk_begin(n, tid), q = step_chunk_begin(n, tid + 1);  // empty from thread kStepChunks on
   auto step_value = [&](int i) {
     return last_value ? tv[i] : tv[i] / static_cast<double>(tz[i] - ta[i]);
   };
@@ -247,7 +246,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) vo
     }
   }
   __syncthreads();
-  if (p < q) {
+  if (tid < kStepChunks && p < q) {
     double A = s_in[tid][0], G = s_in[tid][1], vn = v_right;
     for (int i = q - 1; i >= p; --i) {
       const double vi = step_value(i), ri = tr[i];
