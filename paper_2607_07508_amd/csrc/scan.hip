@@ -425,12 +425,15 @@ struct ScanTokens {
     for (int j = kScanPer - 1; j >= 0; --j) {
       if (j >= n) continue;
       const int64_t t = c0 + j;
-      if (t < bs) {  // rarely: into the trajectory on the left
-        while (t < bs && b > 0) {  // (past empty ones)
-          --b;
-          be = bs;
+      if (t < bs) {  // rarely: into the trajectory on the left, past empty ones by bisection (200,000 of
+                     // them between two tokens: 0.12 ms a call, 50 ms one after another)
+        if (b > 0) --b;
+        bs = cu[b];
+        if (t < bs) {
+          b = find_segment(cu, 0, b, t);
           bs = cu[b];
         }
+        be = cu[b + 1];
         k = segment_kappa(be - bs, gamma, lam, alpha);
       }
       if (t + 1 == be) end();

@@ -77,3 +77,30 @@ def test_nonfinite_stays_in_its_trajectory(lengths, bad):
         ra, rr, _ = oracle.advantage(v[s:e], r[s:e], mask[s:e], np.array([0, e - s], np.int32), 1.0, 1.0, 1.5)
         assert (np.abs(adv[s:e] - ra) <= TOL_ADV * np.maximum(1.0, np.abs(ra))).all()
         assert (np.abs(ret[s:e] - rr) <= TOL_ADV * np.maximum(1.0, np.abs(rr))).all()
+
+
+@pytest.mark.parametrize("lengths", [
+    [1] + [0] * 200_000 + [4096],                    # between two tokens of one thread
+    [2045, 0, 0, 5] + [0] * 70_000 + [1, 2000, 0],   # across a tile edge
+    [0] * 100_000 + [300, 0, 0, 1, 1],               # before the first token of a one-tile batch
+])
+def test_many_empty_trajectories(lengths):
+    """Empty trajectories change nothing and cost a search, not a walk: well under 5 ms a call (tens of
+    milliseconds when a thread steps over them one by one)."""
+    v, r, mask, cu = _batch(lengths, 4)
+    full = [n for n in lengths if n]
+    say(f"flat scan: {len(lengths) - len(full)} empty trajectories among {len(full)}")
+    a = _run(v, r, mask, cu, 1.0, 0.9, 1.5)
+    b = _run(v, r, mask, np.concatenate([[0], np.cumsum(full)]).astype(np.int32), 1.0, 0.9, 1.5)
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
+    args = [torch.from_numpy(x).cuda() for x in (v, r, mask, cu)]
+    times = []
+    for _ in range(5):
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        sao.advantage(*args, 1.0, 0.9, 1.5)
+        stop.record()
+        stop.synchronize()
+        times.append(start.elapsed_time(stop))
+    say(f"median {sorted(times)[2]:.3f} ms")
+    assert sorted(times)[2] < 5.0
