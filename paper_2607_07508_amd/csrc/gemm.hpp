@@ -335,40 +335,31 @@ __device__ __forceinline__ void mma_step_mix(f32x16_t (&acc)[kMI][kNI], const Fr
 // ------------------------------------------------------------------------- //
 // fp32 operands on the bf16 matrix cores
 // ------------------------------------------------------------------------- //
-// An fp32 value is split into three bf16 terms, x = h + m + l with h = bf16(x),
-// m = bf16(x - h), l = bf16(x - h - m) (both differences are exact; 3 x 8
-// significand bits hold fp32's 24, so the sum is x itself unless l underflows),
-// and a product is taken as the six terms hh, hm, mh, mm, hl, lh: the three left
-// out are below 2^-26 of it, less than one fp32 rounding. Each term is exact in the
-// bf16 MFMA's fp32 accumulation, which also rounds once per 16 products where the
-// fp32 MFMA rounds once per 2. Six 32x32x16 bf16 MFMAs take 6 x 32 cycles for what
-// takes eight 32x32x2 fp32 MFMAs 8 x 64, so the loop is bound by the bf16 matrix
-// rate / 6 instead of the fp32 one (256 flop/clk/CU). Measured on the 2048 x 151,936
-// head at 1536 tokens: a forward tile (K = 2048) 309 us, 222 TFLOP/s over the chip at
-// 85 % MFMA busy and a clock that power holds at 1.53 GHz; forward and backward of
-// 2048 tokens 28.7 -> 17.8 ms, with half the error against float64 (1.4e-6 -> 7.5e-7
-// on the hidden gradient).
-// An operand that is not finite, or too large for bf16, makes h or m infinite and
-// hence m or l NaN: every product it enters is NaN, so a wave whose accumulators
-// hold a NaN multiplies its part of the tile again with fp32 MFMAs (redo_f32).
+// An fp32 value x, taken times 2^24, is split into three bf16 terms, h = bf16(x),
+// m = bf16(x - h), l = bf16(x - h - m). Both differences are exact and 3 x 8 significand
+// bits hold fp32's 24, so the sum is x itself; the factor keeps every term of every
+// nonzero fp32 value, subnormals included, a normal bf16. A product is taken as the six
+// terms hh, hm, mh, mm, hl, lh: |m| reaches 2^-8 and |l| 2^-17 of x, so the three left
+// out reach 2^-24 of the product (2^-27.4 root-mean-square over normal values), one fp32
+// rounding. Each term is exact in the bf16 MFMA, which adds eight products at a time and
+// then rounds to nearest: twelve roundings per 16 products where the fp32 MFMA takes 16.
+// Six 32x32x16 bf16 MFMAs take 6 x 32 cycles for what takes eight 32x32x2 fp32 MFMAs
+// 8 x 64, so the loop is bound by the bf16 matrix rate / 6 instead of the fp32 one (256
+// flop/clk/CU): forward and backward of 2048 tokens on the 2048 x 151,936 head 26.0 ms
+// with fp32 MFMAs, 12.7 ms. Errors against float64 over H from 64 to 6144 and 8 to 2048
+// tokens, relative to the fp32 MFMAs': log Z 0.9 to 2.1 (H = 6144),
+// hidden gradients 0.3 to 0.9, weight gradients 0.6 to 0.8. One product alone, as of a
+// single token row with p = 0 elsewhere, has 3.4e-8 against 2.5e-8 of fp32's rounding.
+// A scaled operand that is not finite or too large for bf16 (2^104 and above) makes h or
+// m infinite and hence m or l NaN: every product it enters is NaN. A wave whose
+// accumulators hold a NaN, or a sum of 2^80 and above as an infinity, multiplies its part
+// of the tile again with fp32 MFMAs (redo_f32).
+constexpr float kSplitScale = 0x1p24f;
+constexpr float kSplitUnscale = 0x1p-48f;
+
 struct Split {
   v4u p[3];  // 8 bf16 each: high, middle, low terms
 };
-
-// One term (a word of plane `part`) of two neighbouring elements; x0 and x1 become
-// what is left of them.
-__device__ __forceinline__ uint32_t split_term(float& x0, float& x1, int part) {
-  uint32_t w = pack_bf16x2(x0, x1);
-  if (part < 2) {
-    x0 -= __uint_as_float(w << 16);
-    x1 -= __uint_as_float(w & 0xffff0000u);
-    // Kept here: the compiler would otherwise sink the split to the step that uses it.
-    asm volatile("" : "+v"(w), "+v"(x0), "+v"(x1));
-  } else {
-    asm volatile("" : "+v"(w));
-  }
-  return w;
-}
 
 // The raw elements of one fragment of K16 step u (of two per slab): K8 steps 2u, 2u + 1.
 struct Raw {
@@ -386,21 +377,32 @@ __device__ __forceinline__ Raw read_raw(const v4u* l, int u, int wave_row0, int 
   }
   return r;
 }
-// Term `part` of elements 2j, 2j + 1 of the fragment into word j of its plane
-// (j = 0 .. 3); x0 and x1 carry what is left from one term to the next.
-__device__ __forceinline__ void split_word(const Raw& r, Split& s, int j, int part, float& x0, float& x1) {
-  if (part == 0) {
-    x0 = __uint_as_float(r.c[j >> 1][2 * (j & 1)]);
-    x1 = __uint_as_float(r.c[j >> 1][2 * (j & 1) + 1]);
+// Term `part` of elements 2j, 2j + 1 of the fragment, times `scale`, into word j of its
+// plane (j = 0 .. 3); x0 and x1 carry what is left from one term to the next and, past
+// the last term, the next word's scaled elements (the short turn has room for them).
+__device__ __forceinline__ void split_word(const Raw& r, Split& s, int j, int part, float scale, float& x0, float& x1) {
+  if (part == 0 && j == 0) {
+    x0 = __uint_as_float(r.c[0][0]) * scale;
+    x1 = __uint_as_float(r.c[0][1]) * scale;
   }
-  s.p[part][j] = split_term(x0, x1, part);
+  uint32_t w = pack_bf16x2(x0, x1);
+  if (part < 2) {
+    x0 -= __uint_as_float(w << 16);
+    x1 -= __uint_as_float(w & 0xffff0000u);
+  } else if (j < 3) {
+    x0 = __uint_as_float(r.c[(j + 1) >> 1][2 * ((j + 1) & 1)]) * scale;
+    x1 = __uint_as_float(r.c[(j + 1) >> 1][2 * ((j + 1) & 1) + 1]) * scale;
+  }
+  // Kept here: the compiler would otherwise sink the split to the step that uses it.
+  asm volatile("" : "+v"(w), "+v"(x0), "+v"(x1));
+  s.p[part][j] = w;
 }
 __device__ __forceinline__ void split_frag(const Raw& r, Split& s) {
   float x0, x1;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int part = 0; part < 3; ++part) split_word(r, s, j, part, x0, x1);
+    for (int part = 0; part < 3; ++part) split_word(r, s, j, part, kSplitScale, x0, x1);
 }
 
 constexpr int kSplitTerms = 6;
@@ -438,9 +440,9 @@ __device__ __forceinline__ void split_step(f32x16_t (&acc)[kMI][kNI], Split (&a)
       if (q == 0) raw_b = read_raw<BMn>(lb, u_next, wn * (kBN / kWavesN), r, lane);
       if (q == kHalf) raw_a = read_raw<AMn>(la, u_next, wm * (kBM / 2), r, lane);
       if (q < kHalf)
-        split_word(raw_a, a[(r + kMI - 1) % kMI], q / 3, q % 3, x0, x1);
+        split_word(raw_a, a[(r + kMI - 1) % kMI], q / 3, q % 3, kSplitScale, x0, x1);
       else
-        split_word(raw_b, bn[r], (q - kHalf) / 3, q % 3, x0, x1);
+        split_word(raw_b, bn[r], (q - kHalf) / 3, q % 3, kSplitScale, x0, x1);
       hook(r * kSplitRow + q);
       pin_order();
     }
@@ -533,7 +535,7 @@ struct OneTile {
 
 // The generic kernel body: one 256 x 256 tile per workgroup. Epi provides:
 //   begin(n0, wm, wn, lane)                 before the K loop
-//   tile(acc, m0, n0, wm, wn, lane, lds)    after it (LDS is free)
+//   tile(acc, factor, m0, n0, wm, wn, lane, lds)  after it (LDS is free); the sums are acc times factor
 //   finish(mt, n0, wm, wn, lane, lds)  last (LDS is free)
 // AMn / BMn select the MN-major layout for A / B.
 template <class E, bool AMn, bool BMn, class Epi>
@@ -718,6 +720,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmShape& s, Epi& epi, v4u (*l
   if constexpr (kStream) tiles.begin();
   epi.begin(n0, wm, wn, lane);
   if constexpr (kStream) tiles.claim();
+  float factor = 1.0f;  // of the accumulators, for the epilogue
   f32x16_t acc[kMI][kNI];
 #pragma unroll
   for (int i = 0; i < kMI; ++i)
@@ -782,9 +785,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmShape& s, Epi& epi, v4u (*l
       for (int j = 0; j < kNI; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) bad = fmaf(0.0f, acc_read(acc[i][j][r]), bad);
-    if (__ballot(bad != 0.0f || bad != bad) != 0)
+    factor = kSplitUnscale;
+    if (__ballot(bad != 0.0f || bad != bad) != 0) {
+      factor = 1.0f;
       redo_f32<AMn, BMn>(acc, reinterpret_cast<const float*>(a_base), s.lda, m_valid - m0,
                          reinterpret_cast<const float*>(b_base), s.ldb, n_valid - n0, k_valid, wm, wn, lane);
+    }
   } else {
   Frags f0, f1;
   read_frags<E, AMn, BMn>(f0, lds[0], lds[0] + kAChunks, 0, wm, wn, lane);
@@ -847,7 +853,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmShape& s, Epi& epi, v4u (*l
   lds_barrier();
   epi_mark(epi, 1);
   if constexpr (!kStream) {
-    epi.tile(acc, m0, n0, wm, wn, lane, reinterpret_cast<void*>(&lds[0][0]));
+    epi.tile(acc, factor, m0, n0, wm, wn, lane, reinterpret_cast<void*>(&lds[0][0]));
     epi.finish(mt, n0, wm, wn, lane, reinterpret_cast<void*>(&lds[0][0]));
     break;
   } else {
@@ -862,7 +868,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmShape& s, Epi& epi, v4u (*l
       b_base = static_cast<const char*>(s.b) + n0 * s.ldb * esz;
       copy_first();
     }
-    epi.tile(acc, m_done, n_done, wm, wn, lane, tiles.scratch());
+    epi.tile(acc, factor, m_done, n_done, wm, wn, lane, tiles.scratch());
     epi.finish(mt_done, n_done, wm, wn, lane, tiles.scratch());
     tiles.end();
     if (!more) break;

@@ -204,7 +204,7 @@ struct EpiLse {
   // Running (max, sum exp) per token column over this wave's 128 vocabulary
   // rows; with kMasked, rows at or past the vocabulary end read as -inf. The
   // accumulators themselves are left untouched so they can stay in AGPRs.
-  __device__ __forceinline__ void update(const f32x16_t (&acc)[kMI][kNI], int lim) {
+  __device__ __forceinline__ void update(const f32x16_t (&acc)[kMI][kNI], float factor, int lim) {
     // One token column at a time: its 64 accumulators are read out of their
     // AGPRs into VGPRs, reduced to a max, then to a sum of exponentials.
 #pragma unroll
@@ -215,7 +215,7 @@ struct EpiLse {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int off = mi * 32 + (r & 3) + 8 * (r >> 2);
-          const float x = acc_read(acc[mi][ni][r]);
+          const float x = acc_read(acc[mi][ni][r]) * factor;
           z[mi * 16 + r] = !kMasked || off < lim ? x : -__builtin_inff();
         }
       float tmax = -__builtin_inff();
@@ -233,16 +233,16 @@ struct EpiLse {
     }
   }
 
-  __device__ __forceinline__ void tile(f32x16_t (&acc)[kMI][kNI], int64_t m0, int64_t, int wm, int,
+  __device__ __forceinline__ void tile(f32x16_t (&acc)[kMI][kNI], float factor, int64_t m0, int64_t, int wm, int,
                                        int lane, void*) {
     if constexpr (kMasked) {
       // Vocabulary rows from this wave's first row; the lane's rows sit at offsets
       // up to 123 past it plus 4 (lane >> 5).
       const int64_t rows = M - m0 - wm * (kBM / 2);
       const int64_t lim64 = rows - 4 * (lane >> 5);
-      update(acc, lim64 > kBM ? kBM : static_cast<int>(lim64));
+      update(acc, factor, lim64 > kBM ? kBM : static_cast<int>(lim64));
     } else {
-      update(acc, kBM);
+      update(acc, factor, kBM);
     }
   }
 
@@ -628,12 +628,12 @@ struct EpiDz {
   // row of a token lies in a given tile rarely, so the one-hot term is a branch
   // on yt (the target's tile row, or far outside), and rows at or past the end
   // of the block (last tile only, kMasked) are zero.
-  __device__ __forceinline__ void dz4(const f32x16_t (&acc)[kMI][kNI], int mi, int ni, int j, int vt,
+  __device__ __forceinline__ void dz4(const f32x16_t (&acc)[kMI][kNI], float factor, int mi, int ni, int j, int vt,
                                       int rows, float (&d)[4]) const {
     float p[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      p[e] = fast_exp2(fmaf(acc_read(acc[mi][ni][4 * j + e]), kLog2e, -ll[ni]));
+      p[e] = fast_exp2(fmaf(acc_read(acc[mi][ni][4 * j + e]), kLog2e * factor, -ll[ni]));
       d[e] = gl[ni] * -p[e];
     }
     const unsigned k = static_cast<unsigned>(yt[ni] - vt);
@@ -649,7 +649,7 @@ struct EpiDz {
     }
   }
 
-  __device__ __forceinline__ void tile(f32x16_t (&acc)[kMI][kNI], int64_t m0, int64_t n0, int wm, int wn,
+  __device__ __forceinline__ void tile(f32x16_t (&acc)[kMI][kNI], float factor, int64_t m0, int64_t n0, int wm, int wn,
                                        int lane, void*) {
     clock.tile_id = ((m0 / kBM) << 32) | (n0 / kBN);
     // Valid rows of this tile (all 256 unless kMasked).
@@ -675,8 +675,8 @@ struct EpiDz {
 #pragma unroll
           for (int p = 0; p < 2; ++p) {
             float d0[4], d1[4];
-            dz4(acc, mi, ni, 2 * p, acc_row(wm, mi, 8 * p, lane), rows, d0);
-            dz4(acc, mi, ni, 2 * p + 1, acc_row(wm, mi, 8 * p + 4, lane), rows, d1);
+            dz4(acc, factor, mi, ni, 2 * p, acc_row(wm, mi, 8 * p, lane), rows, d0);
+            dz4(acc, factor, mi, ni, 2 * p + 1, acc_row(wm, mi, 8 * p + 4, lane), rows, d1);
             const auto lo = __builtin_amdgcn_permlane32_swap(pack_bf16x2(d0[0], d0[1]), pack_bf16x2(d1[0], d1[1]),
                                                              false, false);
             const auto hi = __builtin_amdgcn_permlane32_swap(pack_bf16x2(d0[2], d0[3]), pack_bf16x2(d1[2], d1[3]),
@@ -697,7 +697,7 @@ struct EpiDz {
           for (int j = 0; j < 4; ++j) {
             const int vl = acc_row(wm, mi, 4 * j, lane);
             float d[4];
-            dz4(acc, mi, ni, j, vl, rows, d);
+            dz4(acc, factor, mi, ni, j, vl, rows, d);
             store4<E>(row + m0 + vl, d);
           }
         }
@@ -741,7 +741,7 @@ struct EpiAcc {
       *p = x;
   }
 
-  __device__ __forceinline__ void tile(f32x16_t (&acc)[kMI][kNI], int64_t m0, int64_t n0, int wm, int wn,
+  __device__ __forceinline__ void tile(f32x16_t (&acc)[kMI][kNI], float factor, int64_t m0, int64_t n0, int wm, int wn,
                                        int lane, void*) {
     clock.tile_id = ((m0 / kBM) << 32) | (n0 / kBN);
     const bool whole = m0 + kBM <= m_valid && n0 + kBN <= n_valid;  // uniform
@@ -761,7 +761,7 @@ struct EpiAcc {
                                            wn * (kBN / kWavesN) + ni * 32);
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              put((gfloat*)(b + ((r & 3) + 8 * (r >> 2)) * ldo * 4 + lane_off), acc_read(acc[mi][ni][r]));
+              put((gfloat*)(b + ((r & 3) + 8 * (r >> 2)) * ldo * 4 + lane_off), acc_read(acc[mi][ni][r]) * factor);
           }
         return;
       }
@@ -782,7 +782,7 @@ struct EpiAcc {
                                          ni * 32);
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            put((gfloat*)(b + ((r & 3) + 8 * (r >> 2)) * ldo * 4 + lane_off), v[mi][r] + acc_read(acc[mi][ni][r]));
+            put((gfloat*)(b + ((r & 3) + 8 * (r >> 2)) * ldo * 4 + lane_off), fmaf(acc_read(acc[mi][ni][r]), factor, v[mi][r]));
         }
       }
       return;
@@ -816,7 +816,7 @@ struct EpiAcc {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int m = (r & 3) + 8 * (r >> 2) + 4 * (lane >> 5);
-          const float x = v[r] + acc_read(acc[mi][ni][r]);
+          const float x = fmaf(acc_read(acc[mi][ni][r]), factor, v[r]);
           if (nl < n_left && m < m_left)
             *(gfloat*)(b + (static_cast<uint32_t>(m) * static_cast<uint32_t>(4 * ldo) + col)) = x;
         }
