@@ -449,40 +449,85 @@ __device__ __forceinline__ void split_step(f32x16_t (&acc)[kMI][kNI], Split (&a)
   }
 }
 
-// The wave's part of the tile by fp32 MFMAs straight from global memory, for
-// operands that the split cannot hold. Lane half h takes k index k + h; rows past
-// the valid range read the last valid one.
+// Four consecutive k of one row of an operand (K-major: a 16-byte chunk).
+template <bool Mn>
+__device__ __forceinline__ v4u load_k4(const float* p, int64_t ld, int64_t k) {
+  if constexpr (Mn) {
+    p += k * ld;
+    return v4u{__float_as_uint(p[0]), __float_as_uint(p[ld]), __float_as_uint(p[2 * ld]), __float_as_uint(p[3 * ld])};
+  } else {
+    return *reinterpret_cast<const v4u*>(p + k);
+  }
+}
+
+// The wave's part of the tile by fp32 MFMAs straight from global memory, for operands
+// that the split cannot hold. Eight k at a time, lane half h taking four of them, with
+// the next eight on their way: 64 MFMAs of 64 cycles cover the eight loads, so a tile
+// takes the fp32 rate's time on top of its own. 2048 tokens on 32,768 rows of H = 2048:
+// forward 1.26 ms, with one NaN row of hidden states 2.29 (with two k at a time, one load
+// after another: 3.02; all by fp32 MFMAs: 1.94); forward and backward 4.82 ms, with that
+// row, which makes all of dW NaN, 11.2 (19.9; 7.7), with a weight row of -inf 7.3 (11.7;
+// 7.7). Rows past the valid range read the last valid one.
 template <bool AMn, bool BMn>
 __device__ __forceinline__ void redo_f32(f32x16_t (&acc)[kMI][kNI], const float* a, int64_t lda, int64_t m_left,
                                          const float* b, int64_t ldb, int64_t n_left, int64_t k_valid, int wm, int wn,
                                          int lane) {
-  int64_t ra[kMI], rb[kNI];
+  const float* ra[kMI];
+  const float* rb[kNI];
 #pragma unroll
   for (int i = 0; i < kMI; ++i) {
     const int64_t r = wm * (kBM / 2) + 32 * i + (lane & 31);
-    ra[i] = (r < m_left ? r : m_left - 1) * (AMn ? 1 : lda);
+    ra[i] = a + (r < m_left ? r : m_left - 1) * (AMn ? 1 : lda);
   }
 #pragma unroll
   for (int i = 0; i < kNI; ++i) {
     const int64_t r = wn * (kBN / kWavesN) + 32 * i + (lane & 31);
-    rb[i] = (r < n_left ? r : n_left - 1) * (BMn ? 1 : ldb);
+    rb[i] = b + (r < n_left ? r : n_left - 1) * (BMn ? 1 : ldb);
   }
 #pragma unroll
   for (int i = 0; i < kMI; ++i)
 #pragma unroll
     for (int j = 0; j < kNI; ++j) acc[i][j] = f32x16_t{};
+  const int half = lane >> 5;
+  const int64_t whole = k_valid & ~int64_t{7};
+  v4u fa[kMI], fb[kNI];
+  auto load = [&](int64_t k) {
+#pragma unroll
+    for (int i = 0; i < kMI; ++i) fa[i] = load_k4<AMn>(ra[i], lda, k + 4 * half);
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) fb[i] = load_k4<BMn>(rb[i], ldb, k + 4 * half);
+  };
+  if (whole > 0) load(0);
 #pragma unroll 1
-  for (int64_t k = lane >> 5; k - (lane >> 5) < k_valid; k += 2) {
+  for (int64_t k = 0; k < whole; k += 8) {
+    v4u ca[kMI], cb[kNI];
+#pragma unroll
+    for (int i = 0; i < kMI; ++i) ca[i] = fa[i];
+#pragma unroll
+    for (int i = 0; i < kNI; ++i) cb[i] = fb[i];
+    load(k + 8 < whole ? k + 8 : k);
+    pin_order();
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < kMI; ++i)
+#pragma unroll
+        for (int j = 0; j < kNI; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(ca[i][e]), __uint_as_float(cb[j][e]),
+                                                           acc[i][j], 0, 0, 0);
+  }
+#pragma unroll 1
+  for (int64_t k = whole + half; k - half < k_valid; k += 2) {
     const bool in = k < k_valid;
-    float fa[kMI], fb[kNI];
+    float xa[kMI], xb[kNI];
 #pragma unroll
-    for (int i = 0; i < kMI; ++i) fa[i] = in ? a[ra[i] + k * (AMn ? lda : 1)] : 0.0f;
+    for (int i = 0; i < kMI; ++i) xa[i] = in ? ra[i][k * (AMn ? lda : 1)] : 0.0f;
 #pragma unroll
-    for (int i = 0; i < kNI; ++i) fb[i] = in ? b[rb[i] + k * (BMn ? ldb : 1)] : 0.0f;
+    for (int i = 0; i < kNI; ++i) xb[i] = in ? rb[i][k * (BMn ? ldb : 1)] : 0.0f;
 #pragma unroll
     for (int i = 0; i < kMI; ++i)
 #pragma unroll
-      for (int j = 0; j < kNI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < kNI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i], xb[j], acc[i][j], 0, 0, 0);
   }
 }
 
