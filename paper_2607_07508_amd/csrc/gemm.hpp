@@ -343,11 +343,19 @@ __device__ __forceinline__ void mma_step_mix(f32x16_t (&acc)[kMI][kNI], const Fr
 // out reach 2^-24 of the product (2^-27.4 root-mean-square over normal values), one fp32
 // rounding. Each term is exact in the bf16 MFMA, which adds eight products at a time and
 // then rounds to nearest: twelve roundings per 16 products where the fp32 MFMA takes 16.
+// Operands that are far smaller than the largest in such a sum are floored to a grid
+// some 2^-8 of its last place, each sum by about 1/500 of a last place downwards: over
+// the 4608 sums of K = 6144 that shifts a logit of unit scale by -5e-7 on average, which
+// log Z, a mean over the vocabulary, keeps (error 8.8e-8 of it, against 4.1e-8 with fp32
+// MFMAs). The accumulators of logits are therefore negated over the middle half of K
+// (with B's factor), so that the shifts cancel: rounded sums grow as k^p, and for any p
+// from 0 to 1 the middle half and the two outer quarters differ by at most 5 % (3.7e-8).
+// In the gradients, where nothing averages it, the shift stays below the roundings.
 // Six 32x32x16 bf16 MFMAs take 6 x 32 cycles for what takes eight 32x32x2 fp32 MFMAs
 // 8 x 64, so the loop is bound by the bf16 matrix rate / 6 instead of the fp32 one (256
 // flop/clk/CU): forward and backward of 2048 tokens on the 2048 x 151,936 head 26.0 ms
 // with fp32 MFMAs, 12.7 ms. Errors against float64 over H from 64 to 6144 and 8 to 2048
-// tokens, relative to the fp32 MFMAs': log Z 0.9 to 2.1 (H = 6144),
+// tokens, relative to the fp32 MFMAs': log Z 0.8 to 1.02 (its own rounding dominates),
 // hidden gradients 0.3 to 0.9, weight gradients 0.6 to 0.8. One product alone, as of a
 // single token row with p = 0 elsewhere, has 3.4e-8 against 2.5e-8 of fp32's rounding.
 // A scaled operand that is not finite or too large for bf16 (2^104 and above) makes h or
@@ -356,6 +364,7 @@ __device__ __forceinline__ void mma_step_mix(f32x16_t (&acc)[kMI][kNI], const Fr
 // of the tile again with fp32 MFMAs (redo_f32).
 constexpr float kSplitScale = 0x1p24f;
 constexpr float kSplitUnscale = 0x1p-48f;
+constexpr int kFlipMinSlabs = 8;  // shorter products keep one sign
 
 struct Split {
   v4u p[3];  // 8 bf16 each: high, middle, low terms
@@ -422,7 +431,7 @@ constexpr int kSplitRow = kSplitTerms * kNI;             // MFMAs of one row of 
 template <bool AMn, bool BMn, class Hook>
 __device__ __forceinline__ void split_step(f32x16_t (&acc)[kMI][kNI], Split (&a)[kMI], const Split (&bc)[kNI],
                                            Split (&bn)[kNI], Raw& raw_a, const v4u* la, const v4u* lb, int u_next,
-                                           int wm, int wn, int lane, Hook&& hook) {
+                                           int wm, int wn, int lane, float scale_b, Hook&& hook) {
   constexpr int kHalf = kSplitRow / 2;
   static_assert(kMI == kNI && kHalf == 12, "one A and one B fragment per row, four words per half row");
 #pragma unroll
@@ -442,7 +451,7 @@ __device__ __forceinline__ void split_step(f32x16_t (&acc)[kMI][kNI], Split (&a)
       if (q < kHalf)
         split_word(raw_a, a[(r + kMI - 1) % kMI], q / 3, q % 3, kSplitScale, x0, x1);
       else
-        split_word(raw_b, bn[r], (q - kHalf) / 3, q % 3, kSplitScale, x0, x1);
+        split_word(raw_b, bn[r], (q - kHalf) / 3, q % 3, scale_b, x0, x1);
       hook(r * kSplitRow + q);
       pin_order();
     }
@@ -541,6 +550,14 @@ __device__ __forceinline__ float acc_read(float x) {
   return r;
 }
 
+// One accumulator element negated in place, for the same reason.
+__device__ __forceinline__ float acc_negate(float x) {
+  float t;
+  asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_xor_b32 %1, 0x80000000, %1\n\tv_accvgpr_write_b32 %0, %1"
+               : "+a"(x), "=&v"(t));
+  return x;
+}
+
 // LDS writes of this thread are complete, then the workgroup barrier. Unlike
 // __syncthreads() this does not wait for outstanding global loads, which keeps
 // the next slab's prefetch in flight across the barrier.
@@ -606,13 +623,18 @@ __device__ __forceinline__ void gemm_body(const GemmShape& s, Epi& epi, v4u (*ld
 // Slab 0 (nothing carried), the steady iterations, then the last three, with one copy
 // of the code for both ends: a short product fetches its code as it runs it (tiny
 // fp32 pass 146.9 -> 145.9 us; the bf16 loop, whose registers would spill, keeps two).
-template <class Slab>
-__device__ __forceinline__ void run_slabs(int nk, Slab&& slab) {
+// With kFlip, flip() runs before the slabs at about a quarter and three quarters of nk.
+template <bool kFlip, class Slab, class Flip>
+__device__ __forceinline__ void run_slabs(int nk, Slab&& slab, Flip&& flip) {
+  const int first = nk / 4, second = nk - 4 < 3 * nk / 4 ? nk - 4 : 3 * nk / 4;
 #pragma unroll 1
   for (int kt = 0; kt < nk;) {
     slab(kt++, std::false_type{});
 #pragma unroll 1
-    for (; kt <= nk - 4; ++kt) slab(kt, std::true_type{});
+    for (; kt <= nk - 4; ++kt) {
+      if (kFlip && nk >= kFlipMinSlabs && (kt == first || kt == second)) flip();
+      slab(kt, std::true_type{});
+    }
   }
 }
 
@@ -795,6 +817,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmShape& s, Epi& epi, v4u (*l
     for (int i = 0; i + 1 < kMI; ++i) split_frag(read_raw<AMn>(lds[0], 0, wm * (kBM / 2), i, lane), a[i]);
     raw_a = read_raw<AMn>(lds[0], 0, wm * (kBM / 2), kMI - 1, lane);
     uint32_t carry = 0;  // whether slab kt + 1 has copies left for this slab's first step
+    float scale_b = kSplitScale;
     auto slab = [&](int kt, auto steady) {
       constexpr bool kSteady = decltype(steady)::value;  // 1 <= kt <= nk - 4: every copy is issued
       const int stage = kt % kStages;
@@ -802,7 +825,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmShape& s, Epi& epi, v4u (*l
       const char* ga1 = slab_ptr(true, kt + 1);
       const char* gb1 = slab_ptr(false, kt + 1);
       constexpr int kEveryNext = kSplitMfmas / kCopyNext;
-      split_step<AMn, BMn>(acc, a, b0, b1, raw_a, lds[stage], lds[stage] + kAChunks, 1, wm, wn, lane, [&](int t) {
+      split_step<AMn, BMn>(acc, a, b0, b1, raw_a, lds[stage], lds[stage] + kAChunks, 1, wm, wn, lane, scale_b, [&](int t) {
         if (t % kEveryNext == kEveryNext - 1 && (kSteady || carry))
           copy_at(kCopyNow + t / kEveryNext, ga1, gb1, cstage);
       });
@@ -815,13 +838,28 @@ __device__ __forceinline__ void gemm_tiles(const GemmShape& s, Epi& epi, v4u (*l
       const char* ga2 = slab_ptr(true, kn);
       const char* gb2 = slab_ptr(false, kn);
       constexpr int kEveryNow = kSplitMfmas / kCopyNow;
-      split_step<AMn, BMn>(acc, a, b1, b0, raw_a, lds[cstage], lds[cstage] + kAChunks, 0, wm, wn, lane, [&](int t) {
+      split_step<AMn, BMn>(acc, a, b1, b0, raw_a, lds[cstage], lds[cstage] + kAChunks, 0, wm, wn, lane, scale_b, [&](int t) {
         if (t % kEveryNow == kEveryNow - 1 && (kSteady || refill)) copy_at(t / kEveryNow, ga2, gb2, stage);
       });
       if (!kSteady && kn == nk - 1 && tail) copy_slab(kn, stage);
       carry = refill;
     };
-    run_slabs(nk, slab);
+    // Before slab kt: the sums so far, B's fragments split for its first step, and
+    // those to come change sign.
+    constexpr bool kFlip = !AMn && !BMn;  // logits
+    run_slabs<kFlip>(nk, slab, [&]() {
+      scale_b = -scale_b;
+#pragma unroll
+      for (int i = 0; i < kNI; ++i)
+#pragma unroll
+        for (int part = 0; part < 3; ++part) b0[i].p[part] ^= 0x80008000u;
+#pragma unroll
+      for (int i = 0; i < kMI; ++i)
+#pragma unroll
+        for (int j = 0; j < kNI; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = acc_negate(acc[i][j][r]);
+    });
     // 0 for finite sums, NaN if any is NaN (or infinite).
     float bad = 0.0f;
 #pragma unroll

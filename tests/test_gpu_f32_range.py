@@ -1,7 +1,7 @@
 """fp32 head products over the whole range of fp32 operands, against float64: magnitudes down to
 subnormals and up to fp32's largest in the forward and in both gradients, on both sides of what
 the three-term split holds (operands below 2^104, sums below 2^80; the kernel multiplies a tile
-beyond them with fp32 MFMAs).
+beyond them with fp32 MFMAs), and the bias of long sums.
 
 Bounds as for ordinary operands: each of the 6 ceil(K / 16) MFMAs of a sum rounds twice (4 allowed)
 by 2^-24 of at most sum |a b|; the terms that the split leaves out reach 2^-24 of |a b|, one more.
@@ -129,3 +129,21 @@ def test_nonfinite_operands_in_later_tiles():
     # other rows of the same tiles come from fp32 MFMAs there: equal within the same bound
     assert (np.abs((lse2 - lse)[keep].cpu().numpy()) <= 2 * tol[keep.cpu().numpy()]).all()
     assert (np.abs((logp2 - logp)[keep].cpu().numpy()) <= 2 * tol[keep.cpu().numpy()]).all()
+
+
+@pytest.mark.parametrize("H", [2048, 6144])
+def test_long_sums_have_no_bias(H):
+    """The mean error of logits (log Z over a vocabulary of one) of unit scale. The matrix cores floor what they
+    align, each of a logit's 12 H / 16 sums by up to about 2^-9 of its last place, one way: -1.6e-7 and -8.4e-7 if
+    they added up. A fifth of that is allowed, and 4 standard errors of the mean."""
+    T, rows = 512, 64
+    say(f"f32 range: bias at H={H}")
+    gen = torch.Generator(device="cuda").manual_seed(H)
+    h = torch.randn((T, H), generator=gen, device="cuda")
+    w = 0.02 * torch.randn((rows, H), generator=gen, device="cuda")
+    y = torch.zeros(T, dtype=torch.int32, device="cuda")
+    z = torch.stack([sao.token_logprob(h, w[v:v + 1], y)[1] for v in range(rows)])
+    err = (z.double() - w.double() @ h.double().t()).cpu().numpy()
+    say(f"mean {err.mean():+.2e}, rms {err.std():.2e}")
+    shift = 12 * H / 16 * 2.0 ** -9 * EPS * 0.02 * np.sqrt(H)
+    assert abs(err.mean()) <= shift / 5 + 4 * err.std() / np.sqrt(err.size)
