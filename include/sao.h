@@ -166,7 +166,9 @@ sao_status_t sao_token_logprob(const void* hidden, int64_t ld_hidden, const void
  * values, rewards, mask are [T]; cu_seqlens is int32 [B+1]. If cu_seqlens does
  * not rise from 0 to T without decreasing, every adv/ret is NaN and the status
  * word gets SAO_STATUS_SEGMENTS. ws: sao_workspace_size(SAO_OP_ADVANTAGE, ...) bytes
- * (768, plus 64 per 2048 tokens above 2048 tokens).
+ * (768 up to 2048 tokens; above, 768 plus 64 per 2048 tokens or part of them,
+ * rounded up to a multiple of 256). 768 bytes are enough for every T: without room
+ * for the rest, one workgroup scans each trajectory, which long ones wait for.
  */
 sao_status_t sao_advantage(const float* values, const float* rewards, const uint8_t* mask,
                            const int32_t* cu_seqlens, int32_t B, int64_t T, double gamma,

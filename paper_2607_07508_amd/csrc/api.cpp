@@ -236,9 +236,9 @@ sao_status_t sao_advantage(const float* values, const float* rewards, const uint
   if (T < 0 || T > kMaxRows) return fail(SAO_ERR_SHAPE, "T=%lld out of range", (long long)T);
   if (sao_status_t s = check_discounts(gamma, lam, alpha)) return s;
   if (T == 0) return ok();
-  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_ADVANTAGE, T, 1, 1, SAO_F32))) return s;
+  if (sao_status_t s = check_ws(ws, ws_bytes, sao::baseline_workspace())) return s;
   return device(sao::launch_advantage(values, rewards, mask, cu_seqlens, B, T, gamma, lam, alpha, adv, ret,
-                                      n_tokens, status, ws, stream),
+                                      n_tokens, status, ws, ws_bytes, stream),
                 "sao_advantage launch");
 }
 

@@ -24,7 +24,7 @@ int launch_backward(const void*, int64_t, const void*, int64_t, const int32_t*, 
   return kNoDevice;
 }
 int launch_advantage(const float*, const float*, const uint8_t*, const int32_t*, int32_t, int64_t, double, double,
-                     double, float*, float*, int64_t*, int32_t*, void*, hipStream_t) {
+                     double, float*, float*, int64_t*, int32_t*, void*, size_t, hipStream_t) {
   return kNoDevice;
 }
 int launch_step_advantage(const float*, const float*, const uint8_t*, const int32_t*, int32_t, int64_t, double,

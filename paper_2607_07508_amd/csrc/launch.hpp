@@ -19,10 +19,12 @@ int launch_backward(const void* hidden, int64_t ld_hidden, const void* w_head, i
                            const int32_t* target, const float* lse, const float* g, int64_t T, int64_t H,
                            int64_t V, bool bf16, void* dhidden, float* dw, bool dw_store, void* ws, hipStream_t st);
 
+// With less than advantage_workspace(T) bytes (at least baseline_workspace()) every
+// trajectory takes one workgroup.
 int launch_advantage(const float* values, const float* rewards, const uint8_t* mask,
                             const int32_t* cu_seqlens, int32_t B, int64_t T, double gamma, double lam,
                             double alpha, float* adv, float* ret, int64_t* n_tokens, int32_t* status,
-                            void* ws, hipStream_t st);
+                            void* ws, size_t ws_bytes, hipStream_t st);
 
 int launch_step_advantage(const float* values, const float* rewards, const uint8_t* mask,
                                  const int32_t* cu_seqlens, int32_t B, int64_t T, double gamma, double lam,

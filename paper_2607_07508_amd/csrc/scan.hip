@@ -644,14 +644,14 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_flat(const float* values,
 // tokens both take a few launches' time whatever the lengths (23 us per call from
 // Python), but for one trajectory among few: 131,071 tokens in one took 183 us with
 // one workgroup and 19 us flat. So trajectories by the CU-full over 2^20 tokens take
-// one workgroup each, everything else the flat scan.
+// one workgroup each, everything else the flat scan, if the workspace holds its tile maps.
 constexpr int64_t kScanFlatTokens = int64_t{1} << 20;
 constexpr int32_t kScanFlatMaxB = 256;
 
 int launch_advantage(const float* values, const float* rewards, const uint8_t* mask,
                             const int32_t* cu_seqlens, int32_t B, int64_t T, double gamma, double lam,
                             double alpha, float* adv, float* ret, int64_t* n_tokens, int32_t* status,
-                            void* ws, hipStream_t st) {
+                            void* ws, size_t ws_bytes, hipStream_t st) {
   const SegHead H = seg_head();
   char* w8 = static_cast<char*>(ws);
   int32_t* bad = reinterpret_cast<int32_t*>(w8 + H.bad);
@@ -665,7 +665,7 @@ int launch_advantage(const float* values, const float* rewards, const uint8_t* m
                        gamma, lam, alpha, adv, ret, n_tokens, nullptr, nullptr, status, vec_ok);
     return hipGetLastError();
   }
-  if (T <= kScanFlatTokens || B < kScanFlatMaxB) {
+  if ((T <= kScanFlatTokens || B < kScanFlatMaxB) && ws_bytes >= advantage_workspace(T)) {
     TileMap* maps = reinterpret_cast<TileMap*>(w8 + H.total);
     const unsigned tiles = static_cast<unsigned>(ceil_div(T, kScanTile));
     hipLaunchKernelGGL(k_scan_tiles, dim3(tiles + 1), dim3(kScanThreads), 0, st, values, rewards, mask, cu_seqlens, B, T,

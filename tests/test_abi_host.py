@@ -239,6 +239,13 @@ def test_workspace_sizes(L):
     assert 0 < ws(binding.OP_VALUE, 32768, 6144, 1, 0) < 32768 * 6144 * 2 // 16
 
 
+@pytest.mark.parametrize("T", [1, 2048, 2049, 4096, 4097, 10240, 10241, 131071, 1 << 20, 1 << 24])
+def test_advantage_workspace_rule(L, T):
+    # as include/sao.h states it
+    maps = 64 * -(-T // 2048) if T > 2048 else 0
+    assert binding.workspace_size(binding.OP_ADVANTAGE, T, 1, 1, 0) == 768 + -(-maps // 256) * 256
+
+
 def _block_rule(T, H, V, esize):
     """The backward's vocabulary block as include/sao.h states it for
     sao_workspace_size."""

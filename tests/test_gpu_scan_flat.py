@@ -58,6 +58,63 @@ def test_flat_scan(name, gamma, lam, alpha):
     assert (np.abs(ret - rr) <= TOL_ADV * np.maximum(1.0, np.abs(rr))).all()
 
 
+def _run_small_workspace(v, r, mask, cu, gamma, lam, alpha, off=0):
+    """sao_advantage with the 768 bytes that every T takes (one workgroup per trajectory), the arrays `off`
+    elements into their storage. Also that nothing past those bytes is written."""
+    dev = []
+    for x in (v, r, mask):
+        t = torch.zeros(len(x) + off, dtype=torch.from_numpy(x[:0]).dtype, device="cuda")
+        t[off:] = torch.from_numpy(x).cuda()
+        dev.append(t[off:])
+    cud = torch.from_numpy(cu).cuda()
+    out = [torch.full((len(v) + off,), 7.0, device="cuda")[off:] for _ in range(2)]
+    n = torch.full((1,), -1, dtype=torch.int64, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.full((4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    code = sao.lib().sao_advantage(*[t.data_ptr() for t in dev], cud.data_ptr(), len(cu) - 1, len(v), gamma, lam, alpha,
+                                   out[0].data_ptr(), out[1].data_ptr(), n.data_ptr(), status.data_ptr(),
+                                   ws.data_ptr(), 768, torch.cuda.current_stream().cuda_stream)
+    assert code == 0, sao.lib().sao_last_error_message()
+    assert (ws[768:] == 0x5a).all()
+    return [x.cpu().numpy() for x in (*out, n)] + [int(status)]
+
+
+@pytest.mark.parametrize("name", [k for k in CASES if k not in ("per trajectory",)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_small_workspace(name, off):
+    v, r, mask, cu = _batch(CASES[name], len(name))
+    say(f"per-trajectory scan: {name}, T={len(mask)} offset={off}")
+    adv, ret, n, status = _run_small_workspace(v, r, mask, cu, 0.97, 0.9, 1.5, off)
+    ra, rr, N = oracle.advantage(v, r, mask, cu, 0.97, 0.9, 1.5)
+    assert int(n[0]) == N and status == 0
+    assert (np.abs(adv - ra) <= TOL_ADV * np.maximum(1.0, np.abs(ra))).all()
+    assert (np.abs(ret - rr) <= TOL_ADV * np.maximum(1.0, np.abs(rr))).all()
+    for i, x in ((len(cu) - 1, len(v) + 5), (0, 1)):
+        bad = cu.copy()
+        bad[i] = x
+        adv, ret, n, status = _run_small_workspace(v, r, mask, bad, 0.97, 0.9, 1.5, off)
+        assert np.isnan(adv).all() and np.isnan(ret).all() and int(n[0]) == N and status == 2
+
+
+@pytest.mark.parametrize("off", [0, 1])
+def test_per_trajectory_rule(off):
+    """Over both limits of the flat scan with the whole workspace: unaligned arrays, then malformed segments."""
+    v, r, mask, cu = _batch([4097] * 300, 6)
+    say(f"per-trajectory scan: T={len(v)} B=300 offset={off}")
+    pad = lambda x: torch.from_numpy(np.concatenate([x[:off], x])).cuda()[off:]  # noqa: E731
+    args = [pad(v), pad(r), pad(mask)]
+    adv, ret, n = sao.advantage(*args, torch.from_numpy(cu).cuda(), 0.97, 0.9, 1.5)
+    ra, rr, N = oracle.advantage(v, r, mask, cu, 0.97, 0.9, 1.5)
+    assert int(n) == N
+    assert (np.abs(adv.cpu().numpy() - ra) <= TOL_ADV * np.maximum(1.0, np.abs(ra))).all()
+    assert (np.abs(ret.cpu().numpy() - rr) <= TOL_ADV * np.maximum(1.0, np.abs(rr))).all()
+    bad = cu.copy()
+    bad[150] = bad[149] - 1
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    adv, ret, n = sao.advantage(*args, torch.from_numpy(bad).cuda(), 0.97, 0.9, 1.5, status=status)
+    assert adv.isnan().all() and ret.isnan().all() and int(n) == N and int(status) == 2
+
+
 @pytest.mark.parametrize("lengths", [[500, 20, 600], [3000, 20, 5000, 2000]])
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
 def test_nonfinite_stays_in_its_trajectory(lengths, bad):
