@@ -89,11 +89,16 @@ __device__ __forceinline__ Seg block_segmented_scan(const Seg& x, const Seg& car
   return seg_combine(before, excl);
 }
 
-// Fewer trajectories than CUs: 1024 threads each, so that the longest one, which the pass
-// waits for, takes a quarter of the tiles, and their counts are added to one address,
-// n_tokens, which the check of the segments has zeroed (64 trajectories of
-// 4096 tokens: 33 -> 24 us with the check and the count).
-constexpr int32_t kStepWideMaxB = 256;
+// Up to this many trajectories their counts are added to one address, n_tokens, which the
+// check of the segments has zeroed, instead of taking a launch to sum the slots (256
+// trajectories of 300 tokens: 16.2 -> 13.1 us with the check and the count).
+constexpr int32_t kStepFewMaxB = 256;
+// No more trajectories than CUs, and long ones: 1024 threads each, so that the longest
+// one, which the pass waits for, takes a quarter of the tiles (64 trajectories of 4096
+// tokens: 27.1 -> 19.5 us). Short ones leave most of the threads idle at the barriers: 200
+// trajectories of 300 tokens take 18.3 us with 1024 threads and 13.2 with 256, of 1000
+// 18.1 and 17.3, of 2000 18.9 and 21.7; 64 of 1000 17.8 and 14.7.
+constexpr int64_t kStepWideMeanTokens = 1536;
 
 template <int THREADS, int kSlots>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_step_advantage(
@@ -313,22 +318,25 @@ int launch_step_advantage(const float* values, const float* rewards, const uint8
   const SegHead H = seg_head();
   int32_t* bad = reinterpret_cast<int32_t*>(w8 + H.bad);
   int64_t* slots = reinterpret_cast<int64_t*>(w8 + H.slots);
-  const bool wide = B <= kStepWideMaxB;
+  const bool few = B <= kStepFewMaxB;
+  const bool wide = few && T >= kStepWideMeanTokens * B;
   hipLaunchKernelGGL((k_check_segments<256, kCountSlots>), dim3(1), dim3(256), 0, st, cu_seqlens, B, T, bad, slots,
-                     status, wide ? n_tokens : nullptr);
+                     status, few ? n_tokens : nullptr);
   // Whole in-trajectory blocks of 8 tokens use vector loads when the bases allow them.
   const bool vec_ok = ((reinterpret_cast<uintptr_t>(values) | reinterpret_cast<uintptr_t>(rewards)) & 15u) == 0 &&
                       (reinterpret_cast<uintptr_t>(mask) & 7u) == 0;
   // The output spans use 16-byte stores when adv and ret are 16-byte aligned and `last` (if given) 4-byte aligned.
   const bool out_vec = ((reinterpret_cast<uintptr_t>(adv) | reinterpret_cast<uintptr_t>(ret)) & 15u) == 0 &&
                        (reinterpret_cast<uintptr_t>(last) & 3u) == 0;
-  const auto kernel = wide ? k_step_advantage<1024, 1> : k_step_advantage<256, kCountSlots>;
+  const auto kernel = !few   ? k_step_advantage<256, kCountSlots>
+                      : wide ? k_step_advantage<1024, 1>
+                             : k_step_advantage<256, 1>;
   hipLaunchKernelGGL(kernel, dim3(B), dim3(wide ? 1024 : 256), 0, st, values, rewards, mask, cu_seqlens, B, T, gamma, lam,
-                     alpha, last_value, adv, ret, last, wide ? n_tokens : slots, bad,
+                     alpha, last_value, adv, ret, last, few ? n_tokens : slots, bad,
                      reinterpret_cast<int32_t*>(w8 + Ly.tab_a), reinterpret_cast<int32_t*>(w8 + Ly.tab_z),
                      reinterpret_cast<double*>(w8 + Ly.tab_v), reinterpret_cast<double*>(w8 + Ly.tab_r), vec_ok,
                      out_vec);
-  if (n_tokens && !wide)
+  if (n_tokens && !few)
     hipLaunchKernelGGL(k_slots_total<kCountSlots>, dim3(1), dim3(64), 0, st, slots, n_tokens);
   return hipGetLastError();
 }

@@ -1,5 +1,6 @@
-"""Step-level and group advantages on both sides of their launch rules (256 trajectories for
-the step-level workgroups, 1024 for the fused group launches), against the oracle."""
+"""Step-level and group advantages on both sides of their launch rules (256 trajectories and a
+mean length of 1536 tokens for the step-level workgroups, 512 trajectories for the fused group
+launches), against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -28,7 +29,8 @@ def _t(x):
     return torch.from_numpy(np.ascontiguousarray(x)).cuda()
 
 
-@pytest.mark.parametrize("B,T", [(1, 8191), (1, 8193), (2, 50_000), (256, 30_000), (257, 30_000)])
+@pytest.mark.parametrize("B,T", [(1, 8191), (1, 8193), (2, 50_000), (256, 30_000), (257, 30_000), (1, 1535), (1, 1536),
+                                 (40, 61_439), (40, 61_440)])
 def test_step_forms(B, T):
     say(f"step forms: B={B} T={T}")
     v, r, m, cu = _batch(B, T, B + T)
@@ -41,7 +43,7 @@ def test_step_forms(B, T):
     assert sao.step_advantage(_t(v), _t(r), _t(m), _t(cu), want_count=False)[3] is None
 
 
-@pytest.mark.parametrize("B,G", [(4, 4), (1024, 8), (1028, 4)])
+@pytest.mark.parametrize("B,G", [(4, 4), (1024, 8), (1028, 4), (512, 512), (512, 64), (520, 520), (513, 27)])
 def test_group_forms(B, G):
     T = 30_000
     say(f"group forms: B={B}")
