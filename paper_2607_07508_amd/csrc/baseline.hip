@@ -193,14 +193,18 @@ __global__ __launch_bounds__(kBaseThreads) void k_broadcast(const uint8_t* mask,
                                                             int32_t G, double eps_stab) {
   constexpr int kSlots = kGroup ? 1 : kCountSlots;
   const int b = blockIdx.x;
-  if constexpr (kGroup)
-    if (threadIdx.x == 0) A[b] = group_advantage_of(R, b, G, eps_stab);
+  double Ab;
+  if constexpr (kGroup) {
+    Ab = group_advantage_of(R, b, G, eps_stab);
+    if (threadIdx.x == 0) A[b] = Ab;
+  }
   if (*bad) {
     malformed_slice<kBaseThreads, kSlots>(mask, B, T, adv, nullptr, nullptr, slots);
     return;
   }
   __shared__ int64_t shi[kBaseThreads / 64];
-  const float a = static_cast<float>(kGroup ? group_advantage_of(R, b, G, eps_stab) : A[b]);
+  if constexpr (!kGroup) Ab = A[b];
+  const float a = static_cast<float>(Ab);
   int64_t cnt = 0;
   walk_span(
       cu[b], cu[b + 1], vec_ok,
@@ -225,9 +229,12 @@ inline unsigned blocks_for(int64_t n) { return static_cast<unsigned>((n + kBaseT
 
 // Up to this many trajectories GRPO's advantage takes two launches: the workgroups check
 // the segments, find their group's moments and add their counts to one address for
-// themselves (64 trajectories of 4096 tokens: 17 -> 11 us of kernels and three launch gaps
-// fewer). That work grows with the trajectories squared, so more take a launch per step.
-constexpr int32_t kGroupFusedMaxB = 1024;
+// themselves. Kernels and launch gaps, two launches against five, for trajectories of 512
+// tokens: 64 in groups of 8 8.3 us against 12.4, 512 in groups of 8 13.9 against 14.1 and
+// in one group 64 against 90 (a group's moments are a serial chain). From then on the
+// counts queue at the address and every workgroup reads all the segments: 1024 in groups
+// of 8 20.8 us against 16.0.
+constexpr int32_t kGroupFusedMaxB = 512;
 
 // Vector access needs 16-byte aligned float arrays and a 4-byte aligned mask.
 bool span_vec_ok(const float* rewards, const uint8_t* mask, const float* adv) {
