@@ -7,6 +7,7 @@ stream. There is no CPU fallback: a missing library raises.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from typing import Optional, Tuple
 
@@ -95,13 +96,22 @@ def lib() -> ctypes.CDLL:
 
 
 class _Plain:
-    """Stands in for _fast while libsao.so is not built: every call is left to Python."""
+    """Stands in for _fast where there is none, or no libsao.so: every call is left to Python."""
 
     def __getattr__(self, name):
         return lambda *args: None
 
 
 _fast_module = None
+
+
+def _load_fast():
+    """The compiled module, or None if it was not built or belongs to another torch."""
+    try:
+        module = importlib.import_module("._fast", __package__)
+    except ImportError:
+        return None
+    return module if getattr(module, "torch", None) == str(torch.__version__) else None
 
 
 def _fast():
@@ -111,7 +121,10 @@ def _fast():
     if _fast_module is None:
         if not os.path.exists(LIB_PATH):
             return _Plain()
-        from . import _fast as module
+        module = _load_fast()
+        if module is None:
+            _fast_module = _Plain()
+            return _fast_module
         L = lib()
         names = ("sao_workspace_size", "sao_advantage", "sao_step_advantage", "sao_group_advantage",
                  "sao_clipped_loss_store", "sao_ppo_loss_store", "sao_explained_variance_store")

@@ -47,17 +47,23 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
-def _build_fast() -> None:
+def _build_fast() -> str:
+    """Compiles the argument marshalling and returns "", or what it lacks: it needs g++ and the Python
+    and torch headers, which libsao.so does not, and the binding does without it."""
     import sysconfig
 
     import torch
     gxx = shutil.which("g++")
     if gxx is None:
-        raise RuntimeError("g++ not found")
+        return "g++ not found"
     root = os.path.dirname(torch.__file__)
+    for header in (os.path.join(sysconfig.get_paths()["include"], "Python.h"),
+                   os.path.join(root, "include", "torch", "csrc", "autograd", "python_variable.h")):
+        if not os.path.exists(header):
+            return f"{header} not found"
     tmp = FAST_MODULE + ".tmp"
     cmd = [gxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DSAO_TORCH="{torch.__version__}"',
            "-isystem", os.path.join(root, "include"),
            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "fast.cpp"), "-o", tmp,
@@ -66,6 +72,7 @@ def _build_fast() -> None:
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: fast.cpp\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, FAST_MODULE)
+    return ""
 
 
 def build(extra=(), verbose: bool = False) -> str:
@@ -73,7 +80,12 @@ def build(extra=(), verbose: bool = False) -> str:
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
         fast = ex.submit(_build_fast)
         objs = list(ex.map(lambda s: _compile(s, list(extra)), SOURCES))
-        fast.result()
+        not_built = fast.result()
+    if not_built:
+        # a module of an earlier build may not fit this library
+        if os.path.exists(FAST_MODULE):
+            os.remove(FAST_MODULE)
+        print(f"{FAST_MODULE} not built, calls are marshalled in Python: {not_built}", file=sys.stderr)
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -89,7 +101,7 @@ def build(extra=(), verbose: bool = False) -> str:
         raise RuntimeError(f"link failed\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     os.replace(ptmp, PROBE_LIB)
     if verbose:
-        print(f"built {LIB}, {FAST_MODULE} and {PROBE_LIB}")
+        print(f"built {LIB}, {'' if not_built else FAST_MODULE + ', '}{PROBE_LIB}")
     return LIB
 
 

@@ -335,4 +335,9 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_fast", nullptr, -1, g_methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fast() { return PyModule_Create(&g_module); }
+// The torch version whose headers this was compiled with is the module's `torch`.
+PyMODINIT_FUNC PyInit__fast() {
+  PyObject* m = PyModule_Create(&g_module);
+  if (m && PyModule_AddStringConstant(m, "torch", SAO_TORCH) < 0) Py_CLEAR(m);
+  return m;
+}

@@ -82,3 +82,42 @@ def test_comparison_and_estimator_calls_reject_bad_arrays():
         sao.running_mean_advantage(rewards, mask, cu, history, seen[:2])
     with pytest.raises(TypeError):
         sao.running_mean_advantage(rewards, mask, cu, history, seen, keys=torch.zeros(2, dtype=torch.int64))
+
+
+def test_calls_without_the_native_marshalling(monkeypatch):
+    """Without _fast.so, or with one built for another torch, the same calls go through Python."""
+    import sys
+    import types
+
+    from paper_2607_07508_amd import binding
+    values, rewards, mask, cu = _adv_args()
+    name = "paper_2607_07508_amd._fast"
+    for module in (None, types.SimpleNamespace(torch="0.0"), types.SimpleNamespace()):  # None: its import fails
+        with monkeypatch.context() as mp:
+            mp.setitem(sys.modules, name, module)
+            mp.setattr(binding, "_fast_module", None)
+            assert binding._load_fast() is None
+            assert binding._fast().advantage(values, rewards, mask, cu) is None
+            with pytest.raises(TypeError):    # the Python code's own check
+                sao.advantage(values, rewards.double(), mask, cu)
+
+
+def test_build_does_without_the_native_marshalling(monkeypatch, tmp_path):
+    """What _fast.so needs beyond the C library may be missing; a compile error is an error."""
+    import sysconfig
+
+    from paper_2607_07508_amd import build as B
+    monkeypatch.setattr(B, "FAST_MODULE", str(tmp_path / "_fast.so"))
+    with monkeypatch.context() as mp:
+        mp.setattr(B.shutil, "which", lambda name: None)
+        assert "g++" in B._build_fast()
+    if B.shutil.which("g++") is None:
+        pytest.skip("no C++ compiler")
+    with monkeypatch.context() as mp:
+        mp.setattr(sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+        assert "Python.h" in B._build_fast()
+    monkeypatch.setattr(B, "CSRC", str(tmp_path))
+    (tmp_path / "fast.cpp").write_text("not C++\n")
+    with pytest.raises(RuntimeError):
+        B._build_fast()
+    assert not (tmp_path / "_fast.so").exists()
