@@ -47,6 +47,21 @@ def _both(monkeypatch, calls):
     return native, python
 
 
+def _same(a, b):
+    """Equal in type, shape, device and every value, NaN in the same places."""
+    return (a.dtype == b.dtype and a.shape == b.shape and a.device == b.device
+            and bool(((a == b) | (a.isnan() & b.isnan())).all()))
+
+
+def test_same_tells_values_apart():
+    a, nan = torch.tensor([1.0, 2.0]), float("nan")
+    assert _same(a, a.clone()) and _same(torch.tensor([nan, 2.0]), torch.tensor([nan, 2.0]))
+    assert _same(torch.empty(0), torch.empty(0))
+    assert not _same(a, torch.tensor([1.0, 9.0])) and not _same(torch.tensor([1, 2]), torch.tensor([5, 9]))
+    assert not _same(torch.tensor([nan, 2.0]), a) and not _same(a, torch.tensor([1.0, nan]))
+    assert not _same(a, a.double()) and not _same(a, a[:, None])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("T", [0, 6, 5000])
 def test_same_outputs(monkeypatch, T):
@@ -62,9 +77,7 @@ def test_same_outputs(monkeypatch, T):
                 assert native[k][0] == python[k][0] == "ok", (k, native[k], python[k])
                 for a, b in zip(native[k][1], python[k][1]):
                     assert (a is None) == (b is None), k
-                    if a is not None:
-                        assert a.dtype == b.dtype and a.shape == b.shape and a.device == b.device, k
-                        assert torch.equal(a, b) or (a.isnan() == b.isnan()).all(), k
+                    assert a is None or _same(a, b), k
 
 
 @pytest.mark.gpu
