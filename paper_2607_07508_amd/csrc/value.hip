@@ -59,14 +59,25 @@ __global__ __launch_bounds__(kValueThreads) void k_value_forward(const typename 
   if (lane == 0) v[t] = acc;
 }
 
-// dH_v is written with non-temporal stores: they leave the memory-side cache to the
-// hidden states, which the value forward reads before and after (32,768 rows of 6144
-// over four sets of inputs in turn: the critic's calls 245 -> 215 us; with the cache
-// full of another kernel's dirty lines 257 -> 264).
+// kStream: dH_v is written with non-temporal stores, which leave the memory-side cache to
+// the hidden states, read by the value forward just before and by this kernel. So where
+// the two together exceed the cache; below, dH_v stays in it for the kernel that reads it
+// next. Value forward and loss in us, plain / non-temporal, of bf16 rows of 6144: in a
+// loop over four sets of inputs (a), after a kernel that leaves the cache dirty (b), and
+// that with a kernel that reads dH_v after it (c):
+//   4096 rows (a) 59 /  53 (b) 67 /  66 (c) 83 /  88
+//   8192          80 /  69     90 /  88    119 / 128
+//   12,288       120 / 102    127 / 112    171 / 167
+//   16,384       150 / 139    170 / 141    229 / 206
+//   32,768       238 / 203    253 / 258    370 / 375
+//   65,536       454 / 427    462 / 477    722 / 721
+// The calls alone gain at every size in a loop, as long as they find the cache their own;
+// in a step between other kernels the largest are even, or up to 3 % slower without the
+// reader counted.
 // Block (row block rb, chunk block cb): dv for kValueRows rows, dH_v for those
 // rows over 256 chunks of H, the partial dw_v of those rows, and (cb == 0) the
 // row block's float64 loss partial.
-template <class E>
+template <class E, bool kStream>
 __global__ __launch_bounds__(kValueThreads) void k_value_rows(
     const typename E::storage* hidden, int64_t ld, const typename E::storage* w, const float* v,
     const float* ret, const uint8_t* mask, int64_t T, int64_t H, TokenCount count,
@@ -119,7 +130,11 @@ __global__ __launch_bounds__(kValueThreads) void k_value_rows(
       float o[P];
 #pragma unroll
       for (int e = 0; e < P; ++e) o[e] = d == 0.0f ? 0.0f : d * wf[e];
-      __builtin_nontemporal_store(narrow(o, E{}), &reinterpret_cast<v4u*>(dhidden + (r0 + i0 + u) * H)[c]);
+      v4u* out = &reinterpret_cast<v4u*>(dhidden + (r0 + i0 + u) * H)[c];
+      if constexpr (kStream)
+        __builtin_nontemporal_store(narrow(o, E{}), out);
+      else
+        *out = narrow(o, E{});
       if (d != 0.0f) {
         float h[P];
         widen(hr[u], h, E{});
@@ -209,14 +224,18 @@ int launch_value_loss(const void* hidden, int64_t ld_hidden, const void* w_v, co
   float* part_dw = reinterpret_cast<float*>(w8 + L.part_dw);
   const int P = bf16 ? BF16::kPerChunk : F32::kPerChunk;
   const dim3 grid(static_cast<unsigned>(L.row_blocks), static_cast<unsigned>(ceil_div(H / P, kValueThreads)));
-  if (bf16)
-    hipLaunchKernelGGL(k_value_rows<BF16>, grid, dim3(kValueThreads), 0, st, static_cast<const uint16_t*>(hidden),
-                       ld_hidden, static_cast<const uint16_t*>(w_v), v, ret, mask, T, H, count,
-                       static_cast<uint16_t*>(dhidden_v), part_loss, part_dw);
-  else
-    hipLaunchKernelGGL(k_value_rows<F32>, grid, dim3(kValueThreads), 0, st, static_cast<const float*>(hidden),
-                       ld_hidden, static_cast<const float*>(w_v), v, ret, mask, T, H, count,
-                       static_cast<float*>(dhidden_v), part_loss, part_dw);
+  const bool stream = 2 * T * H * (bf16 ? 2 : 4) > kMemorySideCacheBytes;
+  if (bf16) {
+    const auto kernel = stream ? k_value_rows<BF16, true> : k_value_rows<BF16, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kValueThreads), 0, st, static_cast<const uint16_t*>(hidden), ld_hidden,
+                       static_cast<const uint16_t*>(w_v), v, ret, mask, T, H, count, static_cast<uint16_t*>(dhidden_v),
+                       part_loss, part_dw);
+  } else {
+    const auto kernel = stream ? k_value_rows<F32, true> : k_value_rows<F32, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kValueThreads), 0, st, static_cast<const float*>(hidden), ld_hidden,
+                       static_cast<const float*>(w_v), v, ret, mask, T, H, count, static_cast<float*>(dhidden_v), part_loss,
+                       part_dw);
+  }
   hipLaunchKernelGGL(k_value_final, dim3(static_cast<unsigned>(ceil_div(H, 64))), dim3(kValueThreads), 0,
                      st, part_dw, part_loss, L.row_blocks, H, count, store, loss_v, dw_v);
   return hipGetLastError();

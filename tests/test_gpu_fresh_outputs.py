@@ -66,6 +66,28 @@ def test_value_loss_store_equals_add(T, H):
         assert all(torch.equal(x, y) for x, y in zip(a, b))
 
 
+@pytest.mark.parametrize("dtype,T", [(torch.bfloat16, 65537), (torch.float32, 32769)])
+def test_value_loss_over_the_cache(dtype, T):
+    """One call whose hidden states and their gradient exceed 256 MiB (non-temporal stores) against the same rows
+    in two calls that don't: each row's gradient comes from that row alone, so it is the same bit for bit."""
+    H = 1024
+    say(f"critic over the cache: T={T} {dtype}")
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    h = torch.randn((T, H), generator=gen, device="cuda").to(dtype)
+    w = torch.randn(H, generator=gen, device="cuda").to(dtype)
+    _, _, ret, v, mask = _inputs(T)
+    n = mask.sum(dtype=torch.int64).reshape(1)
+    loss, dh, dw = sao.value_loss(h, w, v, ret, mask, n_tokens=n)
+    loss2 = torch.zeros(1, dtype=torch.float64, device="cuda")
+    dw2 = torch.zeros(H, device="cuda")
+    dh2 = torch.empty_like(h)
+    for a, b in ((0, T // 2), (T // 2, T)):
+        sao.value_loss(h[a:b], w, v[a:b], ret[a:b], mask[a:b], n_tokens=n, loss=loss2, dw_value=dw2, dhidden=dh2[a:b])
+    assert torch.equal(dh, dh2)
+    # fp32 sums of T terms in another order
+    assert float((loss - loss2).abs()) <= 1e-12 * float(loss) and float((dw - dw2).norm() / dw.norm()) <= 1e-5
+
+
 def test_empty_calls():
     f = torch.empty(0, device="cuda")
     m = torch.empty(0, dtype=torch.uint8, device="cuda")
