@@ -270,11 +270,9 @@ sao_status_t sao_group_advantage(const float* rewards, const uint8_t* mask, cons
   if (!traj_reward || !traj_adv) return fail(SAO_ERR_NULL, "traj_reward and traj_adv are required");
   if (group_size < 1 || B % group_size != 0)
     return fail(SAO_ERR_SHAPE, "B=%d must be a positive multiple of group_size=%d", (int)B, (int)group_size);
-  if (!(eps_stab >= 0.0) || !std::isfinite(eps_stab)) return fail(SAO_ERR_VALUE,
-      "eps_stab must be finite and >= 0");
+  if (!(eps_stab >= 0.0) || !std::isfinite(eps_stab)) return fail(SAO_ERR_VALUE, "eps_stab must be finite and >= 0");
   if (T == 0) return ok();
-  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_GROUP_ADVANTAGE, T, 1, 1,
-      SAO_F32))) return s;
+  if (sao_status_t s = check_ws(ws, ws_bytes, sao_workspace_size(SAO_OP_GROUP_ADVANTAGE, T, 1, 1, SAO_F32))) return s;
   return device(sao::launch_group_advantage(rewards, mask, cu_seqlens, B, T, group_size, eps_stab, adv, traj_reward,
                                             traj_adv, n_tokens, status, ws, stream),
                 "sao_group_advantage launch");
@@ -367,8 +365,7 @@ sao_status_t sao_loss_backward(const void* hidden, int64_t ld_hidden, const void
                                int64_t V, sao_dtype_t dtype, void* dhidden, float* dw_head, void* ws,
                                size_t ws_bytes, hipStream_t stream) {
   return backward("sao_loss_backward launch", hidden, ld_hidden, w_head, ld_w, target, lse, g, T, H, V, dtype,
-                  dhidden,
-                  dw_head, false, ws, ws_bytes, stream);
+                  dhidden, dw_head, false, ws, ws_bytes, stream);
 }
 
 sao_status_t sao_loss_backward_store(const void* hidden, int64_t ld_hidden, const void* w_head, int64_t ld_w,

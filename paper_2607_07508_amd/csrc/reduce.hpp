@@ -67,8 +67,8 @@ __global__ __launch_bounds__(THREADS) void k_mask_count(const uint8_t* mask, int
 
 // The loss-mask count that a pass divides by: the caller's, or the sum of the
 // k_mask_count partials of this call, which every block adds up for itself (a launch
-// of their own for up to 2048 of them would cost more). The partials are not the
-// workspace's other pieces, which the blocks write.
+// of their own for at most 256 of them, in the critic 1024, would cost more). The
+// partials are not the workspace's other pieces, which the blocks write.
 struct TokenCount {
   const int64_t* n;     // or null
   const int64_t* part;

@@ -5,7 +5,7 @@ multiplies with fp32 MFMAs instead.
 
 Bound on a logit: a tile's sum takes 6 ceil(K / 16) MFMAs, each rounding its
 fp32 accumulator a few times (allowed here: 4) by 2^-24 of at most sum |a b|; the
-product terms left out are below 2^-26 of |a b|, less than one more rounding.
+product terms left out reach 2^-24 of |a b|, one more rounding.
 """
 import numpy as np
 import pytest
