@@ -311,8 +311,8 @@ def group_advantage(rewards: torch.Tensor, mask: torch.Tensor, cu_seqlens: torch
         return _done(out)
     T, B, dev = _segment_inputs(rewards, mask, cu_seqlens, status)
     adv = torch.empty(T, dtype=torch.float32, device=dev)
-    traj_reward = torch.empty(B, dtype=torch.float64, device=dev)
-    traj_adv = torch.empty(B, dtype=torch.float64, device=dev)
+    traj_reward = _fresh(T, B, torch.float64, dev)
+    traj_adv = _fresh(T, B, torch.float64, dev)
     n_tok = _fresh(T, 1, torch.int64, dev) if want_count else None
     ws = _workspace(workspace_size(OP_GROUP_ADVANTAGE, T, 1, 1, SAO_F32), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
@@ -342,8 +342,8 @@ def running_mean_advantage(rewards: torch.Tensor, mask: torch.Tensor, cu_seqlens
     _vec(seen, "seen", torch.int64, n_keys, dev)
     _vec(keys, "keys", torch.int32, B, dev, optional=True)
     adv = torch.empty(T, dtype=torch.float32, device=dev)
-    traj_reward = torch.empty(B, dtype=torch.float64, device=dev)
-    traj_adv = torch.empty(B, dtype=torch.float64, device=dev)
+    traj_reward = _fresh(T, B, torch.float64, dev)
+    traj_adv = _fresh(T, B, torch.float64, dev)
     n_tok = _fresh(T, 1, torch.int64, dev) if want_count else None
     ws = _workspace(workspace_size(OP_RUNNING_MEAN_ADVANTAGE, T, 1, 1, SAO_F32), dev)
     if T:  # T == 0 is a no-op: empty tensors carry null pointers
