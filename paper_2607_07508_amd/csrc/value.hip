@@ -60,20 +60,21 @@ __global__ __launch_bounds__(kValueThreads) void k_value_forward(const typename 
 }
 
 // kStream: dH_v is written with non-temporal stores, which leave the memory-side cache to
-// the hidden states, read by the value forward just before and by this kernel. So where
-// the two together exceed the cache; below, dH_v stays in it for the kernel that reads it
-// next. Value forward and loss in us, plain / non-temporal, of bf16 rows of 6144: in a
-// loop over four sets of inputs (a), after a kernel that leaves the cache dirty (b), and
-// that with a kernel that reads dH_v after it (c):
-//   4096 rows (a) 59 /  53 (b) 67 /  66 (c) 83 /  88
-//   8192          80 /  69     90 /  88    119 / 128
-//   12,288       120 / 102    127 / 112    171 / 167
-//   16,384       150 / 139    170 / 141    229 / 206
-//   32,768       238 / 203    253 / 258    370 / 375
-//   65,536       454 / 427    462 / 477    722 / 721
-// The calls alone gain at every size in a loop, as long as they find the cache their own;
-// in a step between other kernels the largest are even, or up to 3 % slower without the
-// reader counted.
+// the hidden states, read by the value forward just before and by this kernel; plain
+// stores leave it to dH_v for the kernel that reads it next. Value forward and loss in us,
+// plain / non-temporal, bf16 rows of 6144, in a loop over four sets of inputs (a), behind
+// a kernel that leaves the cache dirty (b), and both with a kernel that reads dH_v after
+// them and is counted (c, d):
+//                (a)          (b)          (c)          (d)
+//   4096       59 /  54     67 /  67     77 /  79     83 /  88
+//   8192       81 /  70     90 /  89    132 / 125    119 / 128
+//   12,288    120 / 102    127 / 112    173 / 168    171 / 166
+//   16,384    150 / 140    170 / 141    220 / 220    228 / 206
+//   32,768    239 / 204    253 / 258    367 / 368    371 / 376
+//   65,536    455 / 428    463 / 478    727 / 728    722 / 724
+// Rows of 2048, 16,384 of them (64 MiB): 67 / 57, 73 / 72, 91 / 90, 94 / 100. So where the
+// hidden states and dH_v together exceed half of the cache; below, the reader's loss is
+// the larger one. At the largest sizes (b) and (d) lose 1 to 3 %.
 // Block (row block rb, chunk block cb): dv for kValueRows rows, dH_v for those
 // rows over 256 chunks of H, the partial dw_v of those rows, and (cb == 0) the
 // row block's float64 loss partial.
@@ -224,7 +225,7 @@ int launch_value_loss(const void* hidden, int64_t ld_hidden, const void* w_v, co
   float* part_dw = reinterpret_cast<float*>(w8 + L.part_dw);
   const int P = bf16 ? BF16::kPerChunk : F32::kPerChunk;
   const dim3 grid(static_cast<unsigned>(L.row_blocks), static_cast<unsigned>(ceil_div(H / P, kValueThreads)));
-  const bool stream = 2 * T * H * (bf16 ? 2 : 4) > kMemorySideCacheBytes;
+  const bool stream = 2 * T * H * (bf16 ? 2 : 4) > kMemorySideCacheBytes / 2;
   if (bf16) {
     const auto kernel = stream ? k_value_rows<BF16, true> : k_value_rows<BF16, false>;
     hipLaunchKernelGGL(kernel, grid, dim3(kValueThreads), 0, st, static_cast<const uint16_t*>(hidden), ld_hidden,

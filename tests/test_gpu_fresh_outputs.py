@@ -66,9 +66,9 @@ def test_value_loss_store_equals_add(T, H):
         assert all(torch.equal(x, y) for x, y in zip(a, b))
 
 
-@pytest.mark.parametrize("dtype,T", [(torch.bfloat16, 65537), (torch.float32, 32769)])
+@pytest.mark.parametrize("dtype,T", [(torch.bfloat16, 32769), (torch.bfloat16, 65535), (torch.float32, 16385)])
 def test_value_loss_over_the_cache(dtype, T):
-    """One call whose hidden states and their gradient exceed 256 MiB (non-temporal stores) against the same rows
+    """One call whose hidden states and their gradient exceed 128 MiB (non-temporal stores) against the same rows
     in two calls that don't: each row's gradient comes from that row alone, so it is the same bit for bit."""
     H = 1024
     say(f"critic over the cache: T={T} {dtype}")
