@@ -428,12 +428,13 @@ struct ScanTokens {
       if (t < bs) {  // rarely: into the trajectory on the left, past empty ones by bisection (200,000 of
                      // them between two tokens: 0.12 ms a call, 50 ms one after another)
         if (b > 0) --b;
+        be = bs;
         bs = cu[b];
         if (t < bs) {
           b = find_segment(cu, 0, b, t);
           bs = cu[b];
+          be = cu[b + 1];
         }
-        be = cu[b + 1];
         k = segment_kappa(be - bs, gamma, lam, alpha);
       }
       if (t + 1 == be) end();
