@@ -462,11 +462,28 @@ __device__ __forceinline__ CutMap thread_map(const ScanTokens& x, const int32_t*
   return F;
 }
 
-// Trajectories of the first and last token of the tile at t0 (uniform).
+// Trajectories of the first and last token of the tile at t0 (uniform): each by 64 probes
+// at a time, both searches' loads together, so that 4096 trajectories take two rounds of
+// loads where halving takes 24 (131,072 tokens in 512 trajectories 17.7 -> 15.7 us). As
+// find_segment, some trajectory in [0, B) if the segments are malformed.
 __device__ __forceinline__ void tile_segments(const int32_t* cu, int32_t B, int64_t T, int64_t t0, int& lo, int& hi) {
   const int64_t last = t0 + kScanTile < T ? t0 + kScanTile - 1 : T - 1;
-  lo = find_segment(cu, 0, B - 1, t0);
-  hi = static_cast<int64_t>(cu[lo + 1]) > last ? lo : find_segment(cu, lo, B - 1, last);
+  const int lane = threadIdx.x & 63;
+  int a0 = 0, z0 = B - 1, a1 = 0, z1 = B - 1;
+  while (a0 < z0 || a1 < z1) {  // uniform
+    const int s0 = (z0 - a0) / 64 + 1, s1 = (z1 - a1) / 64 + 1;
+    const int64_t i0 = a0 + static_cast<int64_t>(lane) * s0, i1 = a1 + static_cast<int64_t>(lane) * s1;
+    const int32_t c0 = cu[i0 < z0 ? i0 : z0], c1 = cu[i1 < z1 ? i1 : z1];
+    // The last probe at or before the token; lane 0's counts as one.
+    const int l0 = 63 - __builtin_clzll(__ballot(i0 <= z0 && c0 <= t0) | 1);
+    const int l1 = 63 - __builtin_clzll(__ballot(i1 <= z1 && c1 <= last) | 1);
+    a0 += l0 * s0;
+    a1 += l1 * s1;
+    z0 = z0 - a0 < s0 ? z0 : a0 + s0 - 1;
+    z1 = z1 - a1 < s1 ? z1 : a1 + s1 - 1;
+  }
+  lo = a0;
+  hi = a1;
 }
 
 // First launch: block i's tile map; the block after the last tile checks the segments.
@@ -646,8 +663,17 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_flat(const float* values,
 // Python), but for one trajectory among few: 131,071 tokens in one took 183 us with
 // one workgroup and 19 us flat. So trajectories by the CU-full over 2^20 tokens take
 // one workgroup each, everything else the flat scan, if the workspace holds its tile maps.
+// Not batches of brief trajectories, at most 1024 of a mean of up to 128 tokens within 16
+// tiles: the flat scan's threads step over a trajectory's end at almost every token (per
+// trajectory / flat, kernels and gaps: 4096 tokens in 255 trajectories 14.3 / 19.0 us,
+// 8192 in 64 14.3 / 15.9, 16,384 in 1024 17.2 / 19.0, in 2048 20.1 / 18.8, 32,768 in 255
+// 14.8 / 16.0, in 64 14.9 / 13.8, 65,536 in 512 16.2 / 16.9). One long trajectory among
+// them takes 2.6 us per tile there, so 16 tiles bound what the rule can lose to 30 us.
 constexpr int64_t kScanFlatTokens = int64_t{1} << 20;
 constexpr int32_t kScanFlatMaxB = 256;
+constexpr int64_t kScanBriefTokens = 16 * kScanTileTokens;
+constexpr int32_t kScanBriefMaxB = 1024;
+constexpr int64_t kScanBriefMeanTokens = 128;
 
 int launch_advantage(const float* values, const float* rewards, const uint8_t* mask,
                             const int32_t* cu_seqlens, int32_t B, int64_t T, double gamma, double lam,
@@ -666,7 +692,8 @@ int launch_advantage(const float* values, const float* rewards, const uint8_t* m
                        gamma, lam, alpha, adv, ret, n_tokens, nullptr, nullptr, status, vec_ok);
     return hipGetLastError();
   }
-  if ((T <= kScanFlatTokens || B < kScanFlatMaxB) && ws_bytes >= advantage_workspace(T)) {
+  const bool brief = T <= kScanBriefTokens && B <= kScanBriefMaxB && T <= kScanBriefMeanTokens * B;
+  if ((T <= kScanFlatTokens || B < kScanFlatMaxB) && !brief && ws_bytes >= advantage_workspace(T)) {
     TileMap* maps = reinterpret_cast<TileMap*>(w8 + H.total);
     const unsigned tiles = static_cast<unsigned>(ceil_div(T, kScanTile));
     hipLaunchKernelGGL(k_scan_tiles, dim3(tiles + 1), dim3(kScanThreads), 0, st, values, rewards, mask, cu_seqlens, B, T,

@@ -40,6 +40,10 @@ CASES = {
     "empty at both ends": [0, 0, 5000, 0, 0, 1, 3000, 0],
     "many short": [int(x) for x in np.random.default_rng(3).integers(0, 40, 700)],
     "hundreds of tiles": [13, 700_001, 5],
+    "brief, one long": [30] * 300 + [20_000] + [17] * 300,  # mean below 128: one workgroup per trajectory
+    "brief": [128] * 256,                                   # on the rule's edge
+    "not brief": [129] * 250,
+    "more than 1024 brief": [3, 0, 11, 1] * 300,
     "per trajectory": [4097] * 1030,  # over the token and trajectory limits of the flat scan
 }
 
