@@ -480,11 +480,13 @@ __device__ __forceinline__ float dot_chunk<F32>(const v4u& a, const v4u& b) {
 // bytes of a tile's partials, [tile][row]), then the threads' results are merged in
 // a fixed tree. Phase 2: the target logits as dot products, kLanes lanes per row (each takes
 // every kLanes-th 16-byte chunk of the row), then logp = z_y - lse at the row's
-// position. Many rows: 64 per block, which reads a tile's partials in 512-byte runs
-// (94 us at 65,536 tokens, 106 us with 8). Few rows leave a serial chain of loads per
-// thread and most CUs idle, so up to kFinFewRows token rows a block takes 8 (2048
-// tokens 61 -> 12 us, 8192 58 -> 19, 16,384 56 -> 32).
-constexpr int64_t kFinFewRows = 32768;
+// position. Many rows: 64 per block, which reads a tile's partials in 512-byte runs.
+// Few rows leave a serial chain of loads per thread and most CUs idle, so up to
+// kFinFewRows token rows a block takes 8. 64 / 8 rows per block in us, V = 50,257: 2048
+// tokens of H = 256 8.3 / 4.9, of 2048 15.9 / 6.8, of 6144 44 / 13; 8192 tokens 8.9 / 8.0,
+// 17.9 / 16.3, 51 / 34; 12,288 tokens 9.6 / 12.5, 22.5 / 23.2, 56 / 53; 32,768 tokens
+// 14.6 / 24.0, 48 / 54.
+constexpr int64_t kFinFewRows = 10240;
 template <class E, int kRows>
 __global__ __launch_bounds__(256) void k_fwd_finalize(const float2* part, int64_t ldp, int m_groups,
                                                       const typename E::storage* hc, int64_t H,
