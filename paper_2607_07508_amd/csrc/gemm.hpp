@@ -355,10 +355,11 @@ __device__ __forceinline__ void mma_step_mix(f32x16_t (&acc)[kMI][kNI], const Fr
 // 8 x 64, so the loop is bound by the bf16 matrix rate / 6 instead of the fp32 one (256
 // flop/clk/CU): forward and backward of 2048 tokens on the 2048 x 151,936 head 26.0 ms
 // with fp32 MFMAs, 12.7 ms. Errors against float64 over H from 64 to 6144 and 8 to 2048
-// tokens, relative to the fp32 MFMAs': log Z 0.8 to 1.02 (its own rounding dominates),
-// hidden gradients 0.3 to 0.9, weight gradients 0.6 to 0.8. One product alone, as of a
-// single token row with p = 0 elsewhere, has 3.4e-8 against 2.5e-8 of fp32's rounding.
-// A scaled operand that is not finite or too large for bf16 (2^104 and above) makes h or
+// tokens, relative to the fp32 MFMAs': log Z and log-probs 0.8 to 1.05 (their own
+// rounding dominates), hidden gradients 0.3 to 0.8, weight gradients 0.5 to 0.9. One product
+// alone, as of a single token row with p = 0 elsewhere, has 3.4e-8 against 2.5e-8 of
+// fp32's rounding.
+// A scaled operand that is not finite or too large for bf16 (from about 2^104) makes h or
 // m infinite and hence m or l NaN: every product it enters is NaN. A wave whose
 // accumulators hold a NaN, or a sum of 2^80 and above as an infinity, multiplies its part
 // of the tile again with fp32 MFMAs (redo_f32).
