@@ -111,7 +111,8 @@ def _load_fast():
         module = importlib.import_module("._fast", __package__)
     except ImportError:
         return None
-    return module if getattr(module, "torch", None) == str(torch.__version__) else None
+    fits = getattr(module, "torch", None) == str(torch.__version__) and hasattr(torch._C, "_cuda_getCurrentRawStream")
+    return module if fits else None
 
 
 def _fast():
